@@ -1,7 +1,7 @@
 // moe_expert_ffn: grouped SwiGLU experts (Sec. 2.1) over the experts that the
 // slot table marks as resident in the expert cache (Sec. 3.4).
 //
-// bf16 path: two grouped GEMMs on MFMA (v_mfma_f32_32x32x16_bf16), both of the
+// bf16 path: two grouped GEMMs on MFMA, both of the
 // form C[rows of expert e, :] = A[rows, K] . B_s[N, K]^T with K contiguous in
 // both operands:
 //   up   : A = x_perm, B = the gate and up projections of slot s, interleaved
@@ -15,7 +15,7 @@
 // expert_offsets and the slot table into a prefix of row tiles per resident
 // expert; everything stays on the device.
 // Fast path (H and F multiples of 32): `ffn_gemm_bf16_fast`, 256 x 256 x 32
-// tiles, 4 waves of 128 x 128, a four-stage LDS ring filled by direct
+// tiles, 4 waves of 128 x 128, a five-stage LDS ring filled by direct
 // global->LDS DMA.
 // General path (H, F multiples of 8): `ffn_gemm_bf16`, 256 x 128 x 64 tiles,
 // 4 waves, register-staged LDS double buffer with zero-filled K tails.
@@ -487,6 +487,17 @@ __device__ __forceinline__ void lds_dma16(const void* g, void* lds_wave_base) {
   __builtin_amdgcn_global_load_lds(g, (lds_void*)lds_wave_base, 16, 0, 0);
 }
 
+// Raw buffer over `elems` 16-bit values at p, and a 16-byte-per-lane load of it
+// into LDS at byte offset voff (lane) + soff (wave).
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const uint16_t* p, int64_t elems) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, (int)(uint32_t)(elems * 2),
+                                           0x00027000);
+}
+__device__ __forceinline__ void buf_dma16(rsrc_t rs, uint32_t voff, uint32_t soff, void* lds_wave_base) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)lds_wave_base, 16, (int)voff, (int)soff, 0, 0);
+}
+
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding:
 // vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14]).
 template <int N>
@@ -497,26 +508,40 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // ------------------------------------------------------- bf16 fast path
 // 256 x 256 block tiles, K in steps of 32, 4 waves (one per SIMD), each
-// owning a 128 x 128 quarter of the output: 16 MFMA 32x32x16 accumulators,
-// 256 registers, held in the accumulation registers. Per K-step a wave reads
-// 128 + 128 rows of fragments from LDS for 2 x 128 x 128 x 32 flop, which
-// keeps LDS traffic (fragment reads plus DMA writes) under the LDS bandwidth.
-// Operands move from global memory straight into LDS
-// (global_load_lds_dwordx4: each lane deposits 16 bytes at M0 + 16 * lane),
-// with an XOR swizzle applied on the load side by choosing which K-chunk each
-// lane fetches. A ring of four LDS stages keeps three K-steps of loads in
-// flight. Within a step the second half-step's fragments are read while the
-// first half's MFMAs run, then one barrier, then the next step's first
-// fragments are read while the second half's MFMAs run. In each half the
-// eight fragment reads go out within the first four MFMAs (so they have
-// landed before the half ends) and the DMA of a later step (A pieces in the
-// first half, B pieces in the second) is spread over the remaining twelve.
+// owning a 128 x 128 quarter of the output: 8 x 8 accumulators of
+// v_mfma_f32_16x16x32_bf16, 256 registers, held in the accumulation registers.
+// What bounds it is power and the gaps between MFMAs. The chip lowers its clock
+// under MFMA load, and a product in this shape takes less energy than in the
+// 32x32x16 one, whose accumulators are read and written twice as often per
+// flop: a loop of nothing but MFMAs on random data runs at 2000 against 1757
+// TFLOP/s.
+// Operands move from global memory straight into LDS (buffer loads of 16 bytes
+// a lane: each lane deposits its bytes at M0 + 16 * lane; the row is a 32-bit
+// lane offset, the K offset the scalar offset), with an XOR swizzle applied on
+// the load side by choosing which K-chunk each lane fetches. A K-step takes 64
+// bytes of a row, half a cache line, so K-steps are loaded in pairs: the two
+// halves of a line are requested by neighbouring instructions and the second
+// is served by the vector cache. Loaded one step at a time every line was
+// asked of L2 twice (2.37e8 L2 reads a gate/up launch of 8 x 1024 rows, now
+// 1.20e8). A ring of five LDS stages holds the pair in use, the pair that has
+// landed or is landing, and a stage that lets the next pair start while the
+// first stage of the pair in use is still needed by nobody: the loads of a
+// pair are spread evenly over two K-steps (bunched they stall the issue of
+// MFMAs) and have one more K-step to land; the weights, which come from HBM,
+// go first.
+// Within a K-step the upper half of the A fragments is read while the MFMAs of
+// the lower half run, and the next step's B fragments and lower half of A while
+// those of the upper half run, one read after each of the first MFMAs.
+// Measured, both GEMMs, one launch (H 4096, F 14336): 8 experts of 1024 rows
+// 2537 -> 2124 us (1137 -> 1359 TFLOP/s), of 998 to 1077 rows 2778 -> 2390 us;
+// 48 experts of 410 to 12000 rows (H 2048, F 1408) 1662 -> 1466 us; MFMAs run
+// in 70 to 75 % of the cycles, 60 to 62 % before.
 // A tile whose expert has at most 128 rows left is computed by all 4 waves
 // side by side (each 32, 64 or 128 rows x 64 columns), so a ragged last row
 // tile costs in proportion to its rows, on every SIMD.
 // Needs K % 32 == 0.
 namespace fast {
-constexpr int BM = 256, BN = 256, BK = 32, STAGES = 4;
+constexpr int BM = 256, BN = 256, BK = 32, STAGES = 5;
 constexpr int kWaves = 4, kThreads = kWaves * 64;
 constexpr int CPR = BK / 8;                 // 16-byte chunks per tile row
 constexpr int RPW = 128 / BK;               // rows per 256-byte bank window
@@ -535,14 +560,21 @@ constexpr int kMaxPieces = 512;
 constexpr size_t kPieceBytes = 256 * 64 * 16;
 static_assert(BM == BN, "A and B stages share the piece layout");
 static_assert(STAGES * 2 * kStage * 2 <= 160 * 1024, "LDS");
-static_assert(STAGES == 4 || STAGES == 5, "the K loop is written for four or five stages");
-__device__ __forceinline__ int swz(int r, int c) { return c ^ ((r / RPW) % CPR); }
+// row groups g = 0..3 of RPW rows take chunk c at c ^ {0, 2, 3, 1}[g]: any 16
+// lanes that a 16-byte LDS read serves together (16 rows of one chunk, or two
+// groups of rows of one chunk and the other two of its neighbour) then hit
+// each of the 64 banks once
+__device__ __forceinline__ int swz(int r, int c) {
+  const int g = (r / RPW) % CPR;
+  return c ^ (((g & 1) << 1) ^ ((g >> 1) * 3));
+}
 }  // namespace fast
 
-// The fast path addresses one expert's weight matrix, and 256 rows of an
-// activation, with 32-bit byte offsets.
+// The fast path addresses 256 rows of a weight matrix or of an activation with
+// 32-bit byte offsets.
 inline bool fast_path(int64_t H, int64_t F) {
-  return H % fast::BK == 0 && F % fast::BK == 0 && F * H < ((int64_t)1 << 31);
+  return H % fast::BK == 0 && F % fast::BK == 0 && F * H < ((int64_t)1 << 31) &&
+         std::max(H, F) <= ((int64_t)1 << 22);
 }
 
 // Partial tiles the workspace holds for the split tail of either GEMM.
@@ -561,6 +593,16 @@ inline int64_t max_split_pieces(int64_t max_rows, int64_t H, int64_t F, int E) {
 // (LDS reads of the next stage in particular) across it.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// acc += a . b, accumulated in place in the accumulation registers. Written as
+// asm with the accumulator tied: with the builtin and 64 four-register
+// accumulators the register allocator rotates them through copies (five
+// register moves per MFMA in the K loop). The compiler does not see an MFMA
+// here, so idle instructions stand between the last one and the first read of
+// an accumulator, and between their clearing and the first one.
+__device__ __forceinline__ void mfma_acc(f32x4_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
 template <int EPI>
@@ -582,17 +624,14 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
   const int64_t ldc = N_out;
   const int64_t n_tiles = (N_out + kOutN - 1) / kOutN;
 
-  constexpr int kStage4 = STAGES > 4 ? kStage : 8;   // a fifth stage, or only the claim words
-  __shared__ __attribute__((aligned(1024))) uint16_t As0[kStage], As1[kStage], As2[kStage], As3[kStage];
-  __shared__ __attribute__((aligned(1024))) uint16_t Bs0[kStage], Bs1[kStage], Bs2[kStage], Bs3[kStage];
-  __shared__ __attribute__((aligned(1024))) uint16_t As4[kStage4];
-  __shared__ __attribute__((aligned(1024))) uint16_t Bs4[STAGES > 4 ? kStage : 1];
-  uint16_t* const As[5] = {As0, As1, As2, As3, As4};
-  uint16_t* const Bs[5] = {Bs0, Bs1, Bs2, Bs3, Bs4};
+  __shared__ __attribute__((aligned(1024))) uint16_t As0[kStage], As1[kStage], As2[kStage], As3[kStage], As4[kStage];
+  __shared__ __attribute__((aligned(1024))) uint16_t Bs0[kStage], Bs1[kStage], Bs2[kStage], Bs3[kStage], Bs4[kStage];
+  uint16_t* const As[STAGES] = {As0, As1, As2, As3, As4};
+  uint16_t* const Bs[STAGES] = {Bs0, Bs1, Bs2, Bs3, Bs4};
   // The claim broadcast lives in the fifth A stage: it is written and read
-  // between tiles, when no DMA targets that stage (a tile's first STAGES - 1
-  // steps load stages 0 .. STAGES - 2), and s_last after every wave has left
-  // the K loop.
+  // between tiles, when no DMA targets that stage (a tile's prologue loads
+  // stages 0 to 3, and the fifth only after a barrier of its first K-step),
+  // and s_last after every wave has left the K loop.
   int64_t& s_claim = *reinterpret_cast<int64_t*>(As4);
   int& s_piece = *reinterpret_cast<int*>(As4 + 4);
   int& s_last = *reinterpret_cast<int*>(As4 + 6);
@@ -600,8 +639,8 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int frow = lane & 31;                 // fragment row within a 32-row MFMA tile
-  const int fk = lane >> 5;                   // which 8-wide half of a 16-wide K step
+  const int frow = lane & 15;                 // fragment row within a 16-row MFMA tile
+  const int fk = lane >> 4;                   // which 8-wide quarter of a K-step
   const int lrow = lane / CPR;                // row within a DMA piece
   const int lpch = lane % CPR;                // physical chunk this lane fills
 
@@ -684,8 +723,10 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
     if (tid == 0 && !in_tail)
       j_next = __hip_atomic_fetch_add(claim_x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool split_tile = t >= full && split > 1;
-    const int64_t kbeg = split_tile ? piece * ksteps / split : 0;
-    const int64_t nks = split_tile ? (piece + 1) * ksteps / split - kbeg : ksteps;
+    // pieces start at even K-steps (whole 128-byte lines)
+    const int64_t kbeg = split_tile ? (piece * ksteps / split) & ~(int64_t)1 : 0;
+    const int64_t kend = split_tile && piece + 1 < split ? ((piece + 1) * ksteps / split) & ~(int64_t)1 : ksteps;
+    const int64_t nks = kend - kbeg;
     // the last expert whose first tile is at or before t (binary search)
     int e = 0;
     int64_t nt, mt;
@@ -720,15 +761,15 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
     const int64_t n0 = nt * kOutN;
     const int nrows = (int)(row_end - row0);
 
-    // DMA sources: a wave-uniform base per piece plus a 32-bit byte offset
-    // per lane (the K offset is added to the base per step). Rows past the
-    // end of the expert or of the weight read a valid row; their results are
-    // never stored. Inside the K loop the stepped base and the lane offset
-    // pass through empty asm, so the load takes the scalar-base form (SGPR
-    // pair + 32-bit VGPR offset) and the K step costs scalar adds, rather than
-    // 64-bit per-lane pointers stepped with vector adds.
-    const char* const a_base = reinterpret_cast<const char*>(A + row0 * K);
-    const char* b_base[PPW];
+    // DMA sources: raw buffers over the tile's rows of A and of B (EPI 0: the
+    // gate rows and the up rows apart), a 32-bit byte offset per lane and the
+    // K offset as the scalar offset, so a K-step costs one scalar add. Rows
+    // past the end of the expert or of the weight read the tile's first row;
+    // their results are never stored.
+    const int64_t rows_b = min((int64_t)kOutN, N_out - n0);
+    const auto rs_a = make_rsrc(A + row0 * K, nrows * K);
+    const auto rs_b0 = make_rsrc(B0 + ((int64_t)s * N_out + n0) * K, rows_b * K);
+    const auto rs_b1 = make_rsrc((EPI == 0 ? B1 : B0) + ((int64_t)s * N_out + n0) * K, rows_b * K);
     uint32_t a_off[PPW], b_off[PPW];
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
@@ -736,55 +777,34 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
       const int r = piece * ROWS_PER_PIECE + lrow;
       const int lch = swz(r, lpch);
       a_off[i] = (uint32_t)(((r < nrows ? r : 0) * K + lch * 8) * 2);
-      int64_t wrow;
-      if (EPI == 0) {
-        const int grp = piece >> 1;              // 32-row groups: gate, up, gate, up, ...
-        int64_t f = n0 + (grp >> 1) * 32 + (r & 31);
-        if (f >= F) f = 0;
-        b_base[i] = reinterpret_cast<const char*>(((grp & 1) ? B1 : B0) + (int64_t)s * F * H);
-        wrow = f;
-      } else {
-        int64_t h = n0 + r;
-        if (h >= H) h = 0;
-        b_base[i] = reinterpret_cast<const char*>(B0 + (int64_t)s * H * F);
-        wrow = h;
-      }
-      b_off[i] = (uint32_t)((wrow * K + lch * 8) * 2);
+      // EPI 0: 32-row groups gate, up, gate, up, ... (two pieces each)
+      const int wr = EPI == 0 ? (piece >> 2) * 32 + (r & 31) : r;
+      b_off[i] = (uint32_t)(((wr < rows_b ? wr : 0) * K + lch * 8) * 2);
     }
-    auto issue = [&](auto stage_c, int64_t step) {
-      constexpr int stage = decltype(stage_c)::value;
-      const int64_t kb = (kbeg + step) * BK * 2;
+    auto issue_a = [&](auto stage_c, int i, int64_t step) {
+      constexpr int st = decltype(stage_c)::value;
+      buf_dma16(rs_a, a_off[i], (uint32_t)((kbeg + step) * (BK * 2)), As[st] + (wave * PPW + i) * 512);
+    };
+    auto issue_b = [&](auto stage_c, int i, int64_t step) {
+      constexpr int st = decltype(stage_c)::value;
+      buf_dma16(i < PPW / 2 || EPI == 1 ? rs_b0 : rs_b1, b_off[i], (uint32_t)((kbeg + step) * (BK * 2)),
+                Bs[st] + (wave * PPW + i) * 512);
+    };
+    // pieces [i0, i1) of the pair of steps (step, step + 1), both halves of a
+    // line next to each other; steps past the end are left out
+    auto pair_a = [&](auto st0, auto st1, int i0, int i1, int64_t step, int64_t nks) {
 #pragma unroll
       for (int i = 0; i < PPW; ++i) {
-        const char* ab = a_base + kb;
-        const char* bb = b_base[i] + kb;
-        uint32_t ao = a_off[i], bo = b_off[i];
-        asm("" : "+s"(ab), "+s"(bb), "+v"(ao), "+v"(bo));
-        lds_dma16(ab + ao, As[stage] + (wave * PPW + i) * 512);
-        lds_dma16(bb + bo, Bs[stage] + (wave * PPW + i) * 512);
+        if (i < i0 || i >= i1) continue;
+        if (step < nks) issue_a(st0, i, step);
+        if (step + 1 < nks) issue_a(st1, i, step + 1);
       }
     };
-    auto issue_a = [&](auto stage_c, int64_t step) {
-      constexpr int stage = decltype(stage_c)::value;
-      const int64_t kb = (kbeg + step) * BK * 2;
-      const char* ab = a_base + kb;
-      asm("" : "+s"(ab));
+    auto pair_b = [&](auto st0, auto st1, int64_t step, int64_t nks) {
 #pragma unroll
       for (int i = 0; i < PPW; ++i) {
-        uint32_t ao = a_off[i];
-        asm("" : "+v"(ao));
-        lds_dma16(ab + ao, As[stage] + (wave * PPW + i) * 512);
-      }
-    };
-    auto issue_b = [&](auto stage_c, int64_t step) {
-      constexpr int stage = decltype(stage_c)::value;
-      const int64_t kb = (kbeg + step) * BK * 2;
-#pragma unroll
-      for (int i = 0; i < PPW; ++i) {
-        const char* bb = b_base[i] + kb;
-        uint32_t bo = b_off[i];
-        asm("" : "+s"(bb), "+v"(bo));
-        lds_dma16(bb + bo, Bs[stage] + (wave * PPW + i) * 512);
+        if (step < nks) issue_b(st0, i, step);
+        if (step + 1 < nks) issue_b(st1, i, step + 1);
       }
     };
 
@@ -793,140 +813,153 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
     auto run = [&](auto mode_c) {
       constexpr int MODE = decltype(mode_c)::value;
       constexpr bool FULL = MODE == 0;
-      constexpr int MI = FULL ? 4 : MODE;
-      constexpr int NI = FULL ? 4 : 2;
+      constexpr int MI = FULL ? 8 : 2 * MODE;      // 16-row fragments
+      constexpr int NI = FULL ? 8 : 4;             // 16-column fragments
+      constexpr int MH = MI / 2;
       const int rbase = FULL ? (wave >> 1) * 128 : 0;
       const int cbase = FULL ? (wave & 1) * 128 : wave * 64;
 
-      f32x16_t acc[MI][NI];
+      f32x4_t acc[MI][NI];
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) acc[mi][ni][q] = 0.f;
-      bf16x8_t fa0[MI], fb0[NI], fa1[MI], fb1[NI];
-
-      auto rd = [&](auto stage_c, int ks, bf16x8_t (&fa)[MI], bf16x8_t (&fb)[NI]) {
-        constexpr int J = decltype(stage_c)::value;
-        const uint16_t* as = As[J];
-        const uint16_t* bs = Bs[J];
-        const int ch = ks * 2 + fk;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) {
-          const int r = rbase + mi * 32 + frow;
-          fa[mi] = *reinterpret_cast<const bf16x8_t*>(&as[r * BK + swz(r, ch) * 8]);
-        }
-#pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-          const int r = cbase + ni * 32 + frow;
-          fb[ni] = *reinterpret_cast<const bf16x8_t*>(&bs[r * BK + swz(r, ch) * 8]);
+          acc[mi][ni] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          asm volatile("" : "+a"(acc[mi][ni]));
+        }
+      asm volatile("s_nop 7");                     // register writes before the first MFMA
+      // fragments of a K-step: the lower and upper halves of the A rows, and
+      // the B columns of an even and an odd step
+      bf16x8_t fal[MH], fah[MH], fb0[NI], fb1[NI];
+
+      // Half a K-step: the MFMAs of one half of the A rows, in order, with the
+      // fragment reads after its first MFMAs (one each) and four DMA pieces
+      // spread over all of them; the fences keep this order.
+      auto half_step = [&](int half, const bf16x8_t (&fa)[MH], const bf16x8_t (&fb)[NI], int n_rd,
+                           auto&& read, auto&& dma) {
+        constexpr int NM = MH * NI;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          mfma_acc(acc[half * MH + m / NI][m % NI], fa[m / NI], fb[m % NI]);
+#pragma unroll
+          for (int j = 0; j < MH + NI; ++j)
+            if (j < n_rd && min(j, NM - 1) == m) read(j);
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if ((2 * k + 1) * NM / 8 == m) dma(k);
+          __builtin_amdgcn_sched_barrier(0);
         }
       };
-      auto mm = [&](const bf16x8_t (&fa)[MI], const bf16x8_t (&fb)[NI]) {
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-          for (int ni = 0; ni < NI; ++ni)
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mi], fb[ni], acc[mi][ni], 0, 0, 0);
+      auto read_a1 = [&](auto stage_c, int half, int mi, bf16x8_t (&f)[MH]) {
+        const int r = rbase + (half * MH + mi) * 16 + frow;
+        f[mi] = *reinterpret_cast<const bf16x8_t*>(&As[decltype(stage_c)::value][r * BK + swz(r, fk) * 8]);
       };
-      // Wait until at most n steps issued after the awaited one are in flight.
-      auto wait_steps = [&](int64_t n) {
-        if constexpr (STAGES >= 5) {
-          if (n >= 3) {
-            wait_vmcnt<3 * 2 * PPW>();
-            return;
-          }
+      auto read_b1 = [&](auto stage_c, int ni, bf16x8_t (&f)[NI]) {
+        const int r = cbase + ni * 16 + frow;
+        f[ni] = *reinterpret_cast<const bf16x8_t*>(&Bs[decltype(stage_c)::value][r * BK + swz(r, fk) * 8]);
+      };
+      // the next step's fragments in the order its MFMAs take them
+      auto read_next = [&](auto stage_c, int j, bf16x8_t (&fbn)[NI]) {
+        if (j == 0) read_a1(stage_c, 0, 0, fal);
+        else if (j <= NI) read_b1(stage_c, j - 1, fbn);
+        else read_a1(stage_c, 0, j - NI, fal);
+      };
+      // K-steps run in pairs (e, e + 1), e even, over stages J = e mod 5 and
+      // J + 1. After the barrier of the even step stage J has been read by
+      // every wave, so the pair e + 4 can start to load into J + 4 and J; its
+      // last A pieces go out in the next pair's first half-step. The wait in
+      // the odd step is for the pair e + 2: younger are the eight B loads of
+      // the pair e + 4.
+      auto pair_ss = [&](auto j_c, int64_t kt) {
+        constexpr int J = decltype(j_c)::value;
+        using S0 = std::integral_constant<int, J>;
+        using S1 = std::integral_constant<int, (J + 1) % 5>;
+        using S2 = std::integral_constant<int, (J + 2) % 5>;
+        using S3 = std::integral_constant<int, (J + 3) % 5>;
+        using S4 = std::integral_constant<int, (J + 4) % 5>;
+        half_step(0, fal, fb0, MH, [&](int j) { read_a1(S0{}, 1, j, fah); }, [&](int k) {
+          if (k & 1) issue_a(S3{}, 2 + k / 2, kt + 3);
+          else issue_a(S2{}, 2 + k / 2, kt + 2);
+        });
+        lds_barrier();
+        half_step(1, fah, fb0, MH + NI, [&](int j) { read_next(S1{}, j, fb1); }, [&](int k) {
+          if (k & 1) issue_b(S0{}, k / 2, kt + 5);
+          else issue_b(S4{}, k / 2, kt + 4);
+        });
+        half_step(0, fal, fb1, MH, [&](int j) { read_a1(S1{}, 1, j, fah); }, [&](int k) {
+          if (k & 1) issue_b(S0{}, 2 + k / 2, kt + 5);
+          else issue_b(S4{}, 2 + k / 2, kt + 4);
+        });
+        wait_vmcnt<2 * PPW>();
+        lds_barrier();
+        half_step(1, fah, fb1, MH + NI, [&](int j) { read_next(S2{}, j, fb0); }, [&](int k) {
+          if (k & 1) issue_a(S0{}, k / 2, kt + 5);
+          else issue_a(S4{}, k / 2, kt + 4);
+        });
+      };
+      // the same near the end of K: loads and reads past the end left out
+      auto read_all = [&](auto stage_c, bf16x8_t (&fbn)[NI]) {
+#pragma unroll
+        for (int j = 0; j < MH + NI; ++j) read_next(stage_c, j, fbn);
+      };
+      auto pair_gen = [&](auto j_c, int64_t kt) {
+        constexpr int J = decltype(j_c)::value;
+        using S0 = std::integral_constant<int, J>;
+        using S1 = std::integral_constant<int, (J + 1) % 5>;
+        using S2 = std::integral_constant<int, (J + 2) % 5>;
+        using S3 = std::integral_constant<int, (J + 3) % 5>;
+        using S4 = std::integral_constant<int, (J + 4) % 5>;
+        auto none = [](int) {};
+        pair_a(S2{}, S3{}, 2, PPW, kt + 2, nks);
+        half_step(0, fal, fb0, MH, [&](int j) { read_a1(S0{}, 1, j, fah); }, none);
+        if (kt + 1 < nks) {
+          lds_barrier();
+          pair_b(S4{}, S0{}, kt + 4, nks);
+          read_all(S1{}, fb1);
         }
-        if (n >= 2) wait_vmcnt<2 * 2 * PPW>();
-        else if (n == 1) wait_vmcnt<2 * PPW>();
+        half_step(1, fah, fb0, 0, none, none);
+        if (kt + 1 >= nks) return;
+        half_step(0, fal, fb1, MH, [&](int j) { read_a1(S1{}, 1, j, fah); }, none);
+        if (kt + 5 < nks) wait_vmcnt<2 * PPW>();
         else wait_vmcnt<0>();
-      };
-      // One K-step on stage J: DMA of step kt+3 into stage J+3 (mod 4); the
-      // second half-step's fragments are read while the first half's MFMAs
-      // run; wait for step kt+1; barrier; the next step's first fragments are
-      // read while this step's second half runs.
-      auto step = [&](auto j_c, int64_t kt) {
-        constexpr int J = decltype(j_c)::value;
-        if (kt + STAGES - 1 < nks)
-          issue(std::integral_constant<int, (J + STAGES - 1) % STAGES>{}, kt + STAGES - 1);
-        rd(j_c, 1, fa1, fb1);
-        mm(fa0, fb0);
-        wait_steps(min(kt + STAGES - 1, nks - 1) - (kt + 1));
         lds_barrier();
-        if (kt + 1 < nks) rd(std::integral_constant<int, (J + 1) % STAGES>{}, 0, fa0, fb0);
-        mm(fa1, fb1);
+        pair_a(S4{}, S0{}, 0, PPW / 2, kt + 4, nks);
+        if (kt + 2 < nks) read_all(S2{}, fb0);
+        half_step(1, fah, fb1, 0, none, none);
       };
 
-      // Steady state (steps kt + 3 < nks): the same step with every
-      // condition known, so the waits are fixed and exact.
-      auto step_ss = [&](auto j_c, int64_t kt) {
-        constexpr int J = decltype(j_c)::value;
-        constexpr int JN = (J + STAGES - 1) % STAGES;
-        issue_a(std::integral_constant<int, JN>{}, kt + STAGES - 1);
-        rd(j_c, 1, fa1, fb1);
-        mm(fa0, fb0);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        }
-        // outstanding after step kt+1: A and B of steps kt+2 .. kt+STAGES-2,
-        // A of kt+STAGES-1
-        wait_vmcnt<(2 * (STAGES - 3) + 1) * PPW>();
-        lds_barrier();
-        issue_b(std::integral_constant<int, JN>{}, kt + STAGES - 1);
-        rd(std::integral_constant<int, (J + 1) % STAGES>{}, 0, fa0, fb0);
-        mm(fa1, fb1);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 1);
-          __builtin_amdgcn_sched_group_barrier(0x008, 2, 1);
-        }
-      };
-
-      if (0 < nks) issue(I0{}, 0);
-      if (1 < nks) issue(I1{}, 1);
-      if (2 < nks) issue(I2{}, 2);
-      if constexpr (STAGES >= 5)
-        if (3 < nks) issue(I3{}, 3);
-      wait_steps(min((int64_t)STAGES - 1, nks) - 1);
-      // every wave has its own pieces of step 0; the barrier makes that true
-      // of all of them (LDS only: steps 1 and 2 keep loading)
+      pair_b(I0{}, I1{}, 0, nks);
+      pair_a(I0{}, I1{}, 0, PPW, 0, nks);
+      pair_b(I2{}, I3{}, 2, nks);
+      pair_a(I2{}, I3{}, 0, PPW / 2, 2, nks);
+      // the first pair has landed (LDS-only barrier: the second keeps loading)
+      if (nks >= 4) wait_vmcnt<3 * PPW>();
+      else wait_vmcnt<0>();
       lds_barrier();
-      rd(I0{}, 0, fa0, fb0);
+      read_all(I0{}, fb0);
       int64_t kt = 0;
-      for (; kt + STAGES + STAGES - 1 <= nks; kt += STAGES) {
-        step_ss(I0{}, kt);
-        step_ss(I1{}, kt + 1);
-        step_ss(I2{}, kt + 2);
-        step_ss(I3{}, kt + 3);
-        if constexpr (STAGES >= 5) step_ss(I4{}, kt + 4);
+      for (; kt + 14 <= nks; kt += 10) {
+        pair_ss(I0{}, kt);
+        pair_ss(I2{}, kt + 2);
+        pair_ss(I4{}, kt + 4);
+        pair_ss(I1{}, kt + 6);
+        pair_ss(I3{}, kt + 8);
       }
-      for (; kt + STAGES <= nks; kt += STAGES) {
-        step(I0{}, kt);
-        step(I1{}, kt + 1);
-        step(I2{}, kt + 2);
-        step(I3{}, kt + 3);
-        if constexpr (STAGES >= 5) step(I4{}, kt + 4);
+      for (; kt < nks; kt += 10) {
+        pair_gen(I0{}, kt);
+        if (kt + 2 < nks) pair_gen(I2{}, kt + 2);
+        if (kt + 4 < nks) pair_gen(I4{}, kt + 4);
+        if (kt + 6 < nks) pair_gen(I1{}, kt + 6);
+        if (kt + 8 < nks) pair_gen(I3{}, kt + 8);
       }
-      if (kt < nks) step(I0{}, kt);
-      if (kt + 1 < nks) step(I1{}, kt + 1);
-      if (kt + 2 < nks) step(I2{}, kt + 2);
-      if constexpr (STAGES >= 5)
-        if (kt + 3 < nks) step(I3{}, kt + 3);
+      // every wave is past its last fragment reads before the epilogue
+      // rewrites the stages; the last MFMAs' results are written
+      lds_barrier();
+      asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
 
       // A K-piece stores its fp32 partial tile; the piece that arrives last
       // (a device-scope counter per tail tile, ordered by release and acquire
@@ -934,23 +967,14 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
       // arrival order, and writes the output.
       if (split_tile) {
         constexpr int kF4 = fast::kPieceBytes / 16 / 256;       // float4 per thread
-        static_assert(MI * NI * 4 <= kF4, "partial tile layout");
+        static_assert(MI * NI <= kF4, "partial tile layout");
         const int64_t tile_slot = t - full;
         f32x4_t* const P = reinterpret_cast<f32x4_t*>(partial);
         f32x4_t* const mine = P + (tile_slot * split + piece) * (int64_t)kF4 * 256;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-          for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-              f32x4_t v;
-              v[0] = acc[mi][ni][4 * q4];
-              v[1] = acc[mi][ni][4 * q4 + 1];
-              v[2] = acc[mi][ni][4 * q4 + 2];
-              v[3] = acc[mi][ni][4 * q4 + 3];
-              mine[((mi * NI + ni) * 4 + q4) * 256 + tid] = v;
-            }
+          for (int ni = 0; ni < NI; ++ni) mine[(mi * NI + ni) * 256 + tid] = acc[mi][ni];
         __threadfence();
         __syncthreads();
         if (tid == 0) s_last = atomicAdd(&tail[1 + tile_slot], 1) == (int)split - 1;
@@ -960,23 +984,13 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-          for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[mi][ni][q] = 0.f;
+          for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         for (int64_t pc = 0; pc < split; ++pc) {
           const f32x4_t* const src = P + (tile_slot * split + pc) * (int64_t)kF4 * 256;
 #pragma unroll
           for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-              for (int q4 = 0; q4 < 4; ++q4) {
-                const f32x4_t v = src[((mi * NI + ni) * 4 + q4) * 256 + tid];
-                acc[mi][ni][4 * q4] += v[0];
-                acc[mi][ni][4 * q4 + 1] += v[1];
-                acc[mi][ni][4 * q4 + 2] += v[2];
-                acc[mi][ni][4 * q4 + 3] += v[3];
-              }
+            for (int ni = 0; ni < NI; ++ni) acc[mi][ni] += src[(mi * NI + ni) * 256 + tid];
         }
       }
 
@@ -985,7 +999,7 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
       // writes its bf16 results into the tile, 32 rows per stage array, with
       // the 16-byte chunks of a row XOR-swizzled by (row mod 8); then the
       // block stores whole rows with 16-byte coalesced writes.
-      // 32x32 C layout: column lane % 32, rows 8*(q/4) + 4*(lane/32) + q%4.
+      // 16x16 C layout: column lane % 16, rows 4 * (lane / 16) + q.
       constexpr int NOUT = kOutN;                       // output columns of the tile
       // Stage array holding rows [32 b, 32 b + 32) of the tile (b compile-time).
       auto stage_of = [&](auto b_c) -> uint16_t* {
@@ -998,32 +1012,35 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
       };
       // Lane coordinates are made opaque per tile so that the write addresses
       // derived from them are formed here, not hoisted out of the tile loop.
-      int ccol = lane & 31;
-      int crow = (lane >> 5) * 4;
+      int ccol = lane & 15;
+      int crow = (lane >> 4) * 4;
       asm volatile("" : "+v"(ccol), "+v"(crow));
-      // wave's rows: 32-row blocks (rbase / 32) + mi
+      // wave's rows: 32-row blocks (rbase / 32) + mi / 2
       auto write_rows = [&](auto b0_c) {
         constexpr int B0 = decltype(b0_c)::value;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
-          uint16_t* const base = mi == 0 ? stage_of(std::integral_constant<int, B0>{})
-                               : mi == 1 ? stage_of(std::integral_constant<int, B0 + 1>{})
-                               : mi == 2 ? stage_of(std::integral_constant<int, (B0 + 2) % 8>{})
-                                         : stage_of(std::integral_constant<int, (B0 + 3) % 8>{});
+          uint16_t* const base = mi < 2 ? stage_of(std::integral_constant<int, B0>{})
+                               : mi < 4 ? stage_of(std::integral_constant<int, B0 + 1>{})
+                               : mi < 6 ? stage_of(std::integral_constant<int, (B0 + 2) % 8>{})
+                                        : stage_of(std::integral_constant<int, (B0 + 3) % 8>{});
 #pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            const int r = 8 * (q >> 2) + crow + (q & 3);
+          for (int q = 0; q < 4; ++q) {
+            const int r = (mi & 1) * 16 + crow + q;
             if (EPI == 0) {
+              // 32-column groups: two gate fragments, then the two up fragments
 #pragma unroll
-              for (int p = 0; p < NI / 2; ++p) {
-                const float g = acc[mi][2 * p][q];
-                const float u = acc[mi][2 * p + 1][q];
-                base[off_in(r, cbase / 2 + p * 32 + ccol)] = f32_to_bf16(swiglu(g, u));
-              }
+              for (int p = 0; p < NI / 4; ++p)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                  const float g = acc[mi][4 * p + hh][q];
+                  const float u = acc[mi][4 * p + 2 + hh][q];
+                  base[off_in(r, cbase / 2 + p * 32 + hh * 16 + ccol)] = f32_to_bf16(swiglu(g, u));
+                }
             } else {
 #pragma unroll
               for (int ni = 0; ni < NI; ++ni)
-                base[off_in(r, cbase + ni * 32 + ccol)] = f32_to_bf16(acc[mi][ni][q]);
+                base[off_in(r, cbase + ni * 16 + ccol)] = f32_to_bf16(acc[mi][ni][q]);
             }
           }
         }

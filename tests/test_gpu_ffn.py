@@ -84,6 +84,17 @@ def test_bf16_split_k_tail(counts, H, F):
     np.testing.assert_array_equal(got, again)
 
 
+@pytest.mark.parametrize("H,F", [
+    (32, 64), (64, 96), (96, 32), (128, 160),      # 1 to 5 K-steps: prologue and tail only
+    (416, 448), (480, 512), (544, 576),            # 13 to 18: around the first steady round
+    (768, 800), (1120, 832),                       # 24 to 26 and 35: around the second
+])
+def test_bf16_k_loop_edges(H, F):
+    # every remainder of the K loop's pairs and rounds in each row mode (full
+    # tile, 128, 64 and 32 rows left); bound of the other bf16 cases
+    _run([290, 129, 70, 20, 256], H, F, None, 5, seed=H + F)
+
+
 def test_bf16_resident_subset_and_slot_order():
     counts = [100, 200, 50, 300, 10, 0]
     slot = [2, -1, 0, -1, 1, 3]
