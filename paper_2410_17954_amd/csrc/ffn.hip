@@ -45,11 +45,57 @@ constexpr int kMaxTailTiles = 1024;
 constexpr int kTailWords = 1 + kMaxTailTiles;
 constexpr int kCounterWords = kClaimWords + 2 * kTailWords;
 
+// Experts with few rows go through their own kernel (below) in items of at
+// most kSmallRows rows: item = expert | chunk << 8, chunk c being the expert's
+// rows kSmallRows * c on. Items with the most 16-row tiles come first, so the
+// costliest units start first.
+constexpr int kSmallMaxTiles = 6;
+constexpr int kSmallRows = 16 * kSmallMaxTiles;
+constexpr int kMaxExperts = 256;
+// chunks beyond each expert's first that a launch without the large tiles may hold
+constexpr int kMaxExtraItems = 176;
+constexpr int kMaxItems = kMaxExperts + kMaxExtraItems;
+
+// Rows of expert e, 0 when it is not resident; *lo: its first row.
+__device__ __forceinline__ int64_t expert_rows(const int32_t* offsets, const int32_t* slot, int e,
+                                               int S, int64_t max_rows, int64_t* lo_out) {
+  const int s = slot ? slot[e] : e;
+  int64_t lo = offsets[e], hi = offsets[e + 1];
+  lo = lo < 0 ? 0 : (lo > max_rows ? max_rows : lo);
+  hi = hi < lo ? lo : (hi > max_rows ? max_rows : hi);
+  if (lo_out) *lo_out = lo;
+  return (s < 0 || s >= S) ? 0 : hi - lo;
+}
+
+// The item list of the experts whose 16-row tile counts are in tiles[0, E)
+// (LDS; 0 = not listed): every thread e < E places its expert's items at their
+// rank. Returns the number of items (every thread). At most cap items are kept.
+__device__ __forceinline__ int list_items(const int32_t* tiles, int E, int e, int32_t* list, int cap) {
+  const int mine = e < E ? tiles[e] : 0;
+  const int my_full = mine > 0 ? (mine - 1) / kSmallMaxTiles : 0;   // chunks of 6 tiles before the last
+  const int my_rem = mine - my_full * kSmallMaxTiles;               // tiles of the last chunk
+  int full = 0, full_before = 0, last = 0, last_before = 0;
+  for (int q = 0; q < E; ++q) {
+    const int t = tiles[q];
+    const int f = t > 0 ? (t - 1) / kSmallMaxTiles : 0;
+    const int r = t - f * kSmallMaxTiles;
+    full += f;
+    last += t > 0;
+    full_before += q < e ? f : 0;
+    last_before += r > my_rem || (r == my_rem && q < e);
+  }
+  if (mine > 0) {
+    for (int c = 0; c < my_full; ++c)
+      if (full_before + c < cap) list[full_before + c] = e | (c << 8);
+    if (full + last_before < cap) list[full + last_before] = e | (my_full << 8);
+  }
+  return min(full + last, cap);
+}
+
 // Per-expert row-tile prefix of resident experts; also clears the counters.
 // Resident experts with at most 16 * small_tiles rows (small_tiles 0 or
 // kSmallMaxTiles) get no row tiles here: they are listed for the few-row
-// kernel instead (small[0] = their number, small[1..] = their ids, those with
-// the most 16-row tiles first, ascending ids within a tile count).
+// kernel instead (small[0] = their number, small[1..] = their items).
 // With split_small an expert's last row tile, when it holds at most bm / 8
 // rows, is counted apart (prefix2: 0 or 1 per expert), so that the GEMMs can
 // run every expert's full-cost row tiles first and these small ones last: a
@@ -57,59 +103,58 @@ constexpr int kCounterWords = kClaimWords + 2 * kTailWords;
 // beside it, so kept in its column group it runs ahead of the tiles that share
 // its weights in L2 and streams them from HBM alone. A last tile of more than
 // bm / 8 rows keeps close enough pace to stay in place.
-constexpr int kSmallMaxTiles = 6;              // few-row experts: at most 96 rows
-
-__global__ void ffn_tiles_kernel(const int32_t* __restrict__ offsets,
-                                 const int32_t* __restrict__ slot, int E, int S,
-                                 int64_t max_rows, int bm, int small_tiles, int split_small,
-                                 int32_t* __restrict__ prefix) {
-  if (blockIdx.x != 0) return;
-  for (int q = threadIdx.x; q < kCounterWords; q += blockDim.x) prefix[E + 1 + q] = 0;
-  if (threadIdx.x != 0) return;
+// One thread per expert and a block scan: walked by one thread the lists took
+// 12 us (60 experts) to 28 us (with 47 few-row experts) of a decode step.
+__global__ void __launch_bounds__(kMaxExperts)
+ffn_tiles_kernel(const int32_t* __restrict__ offsets, const int32_t* __restrict__ slot, int E,
+                 int S, int64_t max_rows, int bm, int small_tiles, int split_small,
+                 int32_t* __restrict__ prefix) {
+  __shared__ int32_t tiles[kMaxExperts];
+  __shared__ int32_t wave_run[kMaxExperts / kWave], wave_run2[kMaxExperts / kWave];
   int32_t* const small = prefix + E + 1 + kCounterWords;
   int32_t* const prefix2 = small + E + 1;
-  int32_t run = 0, run2 = 0;
-  int32_t n_of[kSmallMaxTiles + 1] = {};
-  auto rows_of = [&](int e) -> int64_t {
-    const int s = slot ? slot[e] : e;
-    int64_t lo = offsets[e], hi = offsets[e + 1];
-    lo = lo < 0 ? 0 : (lo > max_rows ? max_rows : lo);
-    hi = hi < lo ? lo : (hi > max_rows ? max_rows : hi);
-    return (s < 0 || s >= S) ? 0 : hi - lo;
-  };
-  for (int e = 0; e < E; ++e) {
-    prefix[e] = run;
-    prefix2[e] = run2;
-    const int64_t m = rows_of(e);
-    if (m == 0) continue;
-    if (m <= 16 * small_tiles) {
-      ++n_of[(m + 15) / 16];
-    } else {
-      const int64_t nt = (m + bm - 1) / bm;
-      if (split_small && m - (nt - 1) * bm <= bm / 8) {
-        run += (int32_t)(nt - 1);
-        ++run2;
-      } else {
-        run += (int32_t)nt;
+  const int e = threadIdx.x;
+  int run = 0, run2 = 0;
+  if (e < E) {
+    const int64_t m = expert_rows(offsets, slot, e, S, max_rows, nullptr);
+    const bool few = m > 0 && m <= 16 * small_tiles;
+    tiles[e] = few ? (int)((m + 15) / 16) : 0;
+    if (m > 0 && !few) {
+      run = (int)((m + bm - 1) / bm);
+      if (split_small && m - (int64_t)(run - 1) * bm <= bm / 8) {
+        --run;
+        run2 = 1;
       }
     }
   }
-  prefix[E] = run;
-  prefix2[E] = run2;
-  // few-row experts by descending tile count: the grid strides over their
-  // units in list order, so the costliest units start first
-  int32_t at[kSmallMaxTiles + 1];
-  int32_t n = 0;
-  for (int c = kSmallMaxTiles; c >= 1; --c) {
-    at[c] = n;
-    n += n_of[c];
+  for (int q = threadIdx.x; q < kCounterWords; q += blockDim.x) prefix[E + 1 + q] = 0;
+  const int mine = run, mine2 = run2;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int a = __shfl_up(run, o, kWave), b = __shfl_up(run2, o, kWave);
+    if (lane_id() >= o) {
+      run += a;
+      run2 += b;
+    }
   }
-  small[0] = n;
-  if (n == 0) return;
-  for (int e = 0; e < E; ++e) {
-    const int64_t m = rows_of(e);
-    if (m > 0 && m <= 16 * small_tiles) small[1 + at[(m + 15) / 16]++] = e;
+  if (lane_id() == kWave - 1) {
+    wave_run[e / kWave] = run;
+    wave_run2[e / kWave] = run2;
   }
+  __syncthreads();
+  for (int w = 0; w < e / kWave; ++w) {
+    run += wave_run[w];
+    run2 += wave_run2[w];
+  }
+  if (e < E) {
+    prefix[e] = run - mine;
+    prefix2[e] = run2 - mine2;
+  }
+  if (e == E - 1) {
+    prefix[E] = run;
+    prefix2[E] = run2;
+  }
+  const int n = small_tiles > 0 ? list_items(tiles, E, e, small + 1, E) : 0;
+  if (e == 0) small[0] = n;
 }
 
 // silu(g) * u with the hardware exp2 and reciprocal (about 2 ulp of float32,
@@ -305,66 +350,111 @@ ffn_gemm_bf16(const uint16_t* __restrict__ A, int64_t K,
 }
 
 // ------------------------------------------------------- few rows per expert
-// An expert with at most 16 * kSmallMaxTiles rows (decode-sized batches) is
-// bound by reading its weights once, not by MFMA. A block of four waves owns
-// one unit: SmallShape<EPI>::COLS output columns (weight rows) of one such
-// expert, all of its rows; wave w streams the w-th quarter of the K range of
-// those weight rows with 16x16x32 MFMAs (the expert's rows padded to 16 * MT,
-// MT = ceil(rows / 16)), and the four partial sums are added through LDS.
-// Splitting K inside the block, rather than giving each wave its own columns,
-// keeps the addresses the whole chip reads at one time close together, which
-// DRAM serves faster. A unit has four 16-column tiles of weights per K step
-// (gate and up of 32 columns, or 64 columns of the down projection), so the
-// activation fragments a wave loads (again in every unit of the expert, from
-// L2) are MT/4 of its weight loads; those extra load instructions, not the
-// MFMAs, are what slows the unit as MT grows.
-constexpr int kSmallWaves = 4;
+// An expert with few rows (decode-sized batches) is bound by reading its
+// weights once, not by MFMA. A block owns one unit: COLS output columns
+// (weight rows) of one item of at most 96 rows; its waves split the K range
+// (contiguous parts, in 64-wide blocks), each streaming its part of those
+// weight rows through 16x16x32 MFMAs (the rows padded to 16 * MT), and the
+// partial sums are added through LDS in wave order.
+// Weights are loaded non-temporally, 8 rows x 128 bytes an instruction: whole
+// cache lines. Plain streaming of 1.9 GB this way runs at 6.9 TB/s, with 16
+// rows x 64 bytes, the layout the MFMA takes, at 5.2 (6.0 without the
+// non-temporal hint). Two such loads hold 16 rows x 64 k; lanes l and l ^ 8
+// swap one half of theirs (a row rotation by 8 under a bank mask, one
+// instruction a register), which leaves two MFMA operands: lane (row r, q)
+// holds the 16-byte chunk 2q of the row's line in the first and 2q + 1 in the
+// second, and the activation rows are read in the same order.
+// Two shapes. WIDE, 4 waves and four 16-column weight tiles a unit (32 columns
+// of gate and of up, or 64 of down): fewest activation loads per weight byte.
+// NARROW, 8 waves and one 16-column tile (of gate and of up, or of down): four
+// times the blocks and twice the waves, for launches of so few units that wide
+// ones would leave compute units without work (one expert of width 5632 has
+// 32 wide units in its down projection, 128 narrow ones).
 constexpr int kSmallRC = 2;                      // row tiles per LDS reduction pass
 
-template <int EPI>
+template <int EPI, bool NARROW>
 struct SmallShape {
   static constexpr int NB = EPI == 0 ? 2 : 1;    // gate and up, or down
-  static constexpr int NT = 4 / NB;              // 16-column MFMA tiles per unit
+  static constexpr int NT = NARROW ? 1 : 4 / NB; // 16-column MFMA tiles per unit
   static constexpr int COLS = 16 * NT;
+  static constexpr int WAVES = NARROW ? 8 : 4;
 };
-// K steps of 32 loaded per batch: four while the rows' fragments are few,
-// two for three or more row tiles (registers)
-template <int MT>
-constexpr int small_unroll() { return MT <= 2 ? 4 : 2; }
 
-// MTMAX: the most row tiles of any listed expert the launch supports; each
-// unit takes the body for its expert's tile count (uniform per block).
-template <int EPI, int MTMAX>
-__global__ void __launch_bounds__(64 * kSmallWaves) __attribute__((amdgpu_waves_per_eu(2)))
+// K blocks of 64 loaded per batch: as many as the registers hold beside the
+// accumulators
+template <int MT, bool NARROW>
+constexpr int small_unroll() { return (MT <= 2 ? 2 : 1) * (NARROW ? 2 : 1); }
+
+__device__ __forceinline__ uint32_t ror8_into(uint32_t keep, uint32_t from, bool high) {
+  // lanes 8..15 (high) or 0..7 of each row of 16 take `from` of the lane 8 away
+  return high ? (uint32_t)__builtin_amdgcn_update_dpp((int)keep, (int)from, 0x128, 0xf, 0xc, false)
+              : (uint32_t)__builtin_amdgcn_update_dpp((int)keep, (int)from, 0x128, 0xf, 0x3, false);
+}
+
+// MTMAX: the most row tiles of any item the launch supports; each unit takes
+// the body for its item's tile count (uniform per block).
+// build: the list is made here, by every block for itself (and left in `small`
+// by block 0 for the down projection), instead of coming from the tile-list
+// kernel: saves that launch where nothing needs the large tiles.
+template <int EPI, int MTMAX, bool NARROW>
+__global__ void __launch_bounds__(NARROW ? 512 : 256) __attribute__((amdgpu_waves_per_eu(2)))
 ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __restrict__ B0,
                const uint16_t* __restrict__ B1, int64_t F, int64_t H,
-               const int32_t* __restrict__ offsets, const int32_t* __restrict__ slot,
-               int64_t max_rows, const int32_t* __restrict__ small, uint16_t* __restrict__ C) {
-  using SS = SmallShape<EPI>;
-  constexpr int NB = SS::NB, NT = SS::NT;
+               const int32_t* __restrict__ offsets, const int32_t* __restrict__ slot, int E, int S,
+               int64_t max_rows, int build, int32_t* __restrict__ small,
+               uint16_t* __restrict__ C) {
+  using SS = SmallShape<EPI, NARROW>;
+  constexpr int NB = SS::NB, NT = SS::NT, W = SS::WAVES;
   constexpr int RC = MTMAX < kSmallRC ? MTMAX : kSmallRC;
-  __shared__ f32x4_t part[kSmallWaves][RC][NT][NB][kWave];
+  __shared__ f32x4_t part[W][RC][NT][NB][kWave];
+  __shared__ int32_t s_list[EPI == 0 ? kMaxItems : 1];
+  int n_items;
+  const int32_t* list = small + 1;
+  if (EPI == 0 && build) {
+    // the tile counts live in the reduction buffer, which is not in use yet
+    int32_t* const tiles = reinterpret_cast<int32_t*>(part);
+    static_assert(sizeof(part) >= kMaxExperts * 4, "tile counts");
+    int n = 0;
+    for (int e = threadIdx.x; e < E; e += blockDim.x)
+      tiles[e] = (int)((expert_rows(offsets, slot, e, S, max_rows, nullptr) + 15) / 16);
+    __syncthreads();
+    // E <= 256 <= threads
+    n = list_items(tiles, E, (int)threadIdx.x, s_list, kMaxItems);
+    __syncthreads();
+    n_items = n;
+    list = s_list;
+    if (blockIdx.x == 0) {
+      for (int q = threadIdx.x; q < n; q += blockDim.x) small[1 + q] = s_list[q];
+      if (threadIdx.x == 0) small[0] = n;
+    }
+  } else {
+    n_items = small[0];
+  }
   const int64_t N_out = EPI == 0 ? F : H;        // a multiple of 32 (fast path)
   const int ncb = (int)((N_out + SS::COLS - 1) / SS::COLS);
-  const int64_t units = (int64_t)small[0] * ncb;
+  const int64_t units = (int64_t)n_items * ncb;
   const int lane = lane_id();
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r = lane & 15;                       // A row / B column of this lane
-  const int kq = (lane >> 4) * 8;                // its 8-wide slice of a K step
-  const int64_t ks = K / 32;
-  const int64_t per = (ks + kSmallWaves - 1) / kSmallWaves;
-  const int64_t kb = min(ks, wave * per), ke = min(ks, kb + per);
-  // byte offset of this lane's B slice from a weight tile's first row
-  const uint32_t b_off = (uint32_t)(((int64_t)r * K + kq) * 2);
+  const int q4 = lane >> 4;                      // its slice of a K step
+  const int64_t k64 = K / 64;
+  const int64_t per = (k64 + W - 1) / W;
+  const int64_t kb = min(k64, wave * per), ke = min(k64, kb + per);
+  const bool odd32 = (K & 32) != 0 && wave == W - 1;   // K's last 32
+  // byte offsets from a weight tile's first row: this lane's slice of an
+  // 8-row x 128-byte load, and of a 16-row x 64-byte one
+  const uint32_t b_off = (uint32_t)(((int64_t)(lane & 7) * K + (lane >> 3) * 8) * 2);
+  const uint32_t b_off32 = (uint32_t)(((int64_t)r * K + q4 * 8) * 2);
+  const uint32_t b_half = (uint32_t)(8 * K * 2);       // the tile's rows 8 to 15
   auto run_unit = [&](auto mt_c, int e, int cb, int m, int64_t lo) {
     constexpr int MT = decltype(mt_c)::value;
-    constexpr int U = small_unroll<MT>();
+    constexpr int U = small_unroll<MT, NARROW>();
     const int s = slot ? slot[e] : e;
     const int64_t kfull = kb + (ke - kb) / U * U;
     const int64_t n0 = (int64_t)cb * SS::COLS;
     // wave-uniform bases plus 32-bit lane offsets. With one row tile, lanes of
     // rows past m load nothing (masked off, so no data comes back) and feed
-    // zeros; with more, every lane loads (rows past m read the expert's last
+    // zeros; with more, every lane loads (rows past m read the item's last
     // row, whose products land in rows that are never stored): most of those
     // lanes are live, and the masks would cost registers.
     const char* const a_base = reinterpret_cast<const char*>(A + lo * K);
@@ -373,7 +463,7 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       a_on[i] = 16 * i + r < m;
-      a_off[i] = (uint32_t)(((int64_t)min(16 * i + r, m - 1) * K + kq) * 2);
+      a_off[i] = (uint32_t)((int64_t)min(16 * i + r, m - 1) * K * 2);
     }
     // a column tile past N_out (the last unit of a down projection whose
     // width is an odd multiple of 32) re-reads the unit's first tile and is
@@ -393,40 +483,70 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
       for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[i][j][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    auto steps = [&](int64_t s0, auto n_c) {
+    auto load_w = [&](const char* p) {
+      return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
+    };
+    auto load_a = [&](int i, int64_t kbyte) {
+      return (MT > 1 || a_on[i]) ? *reinterpret_cast<const u32x4_t*>(a_base + kbyte + a_off[i])
+                                 : u32x4_t{0, 0, 0, 0};
+    };
+    auto mfma = [&](f32x4_t& c, const u32x4_t& a, const u32x4_t& w) {
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
+                                                  __builtin_bit_cast(bf16x8_t, w), c, 0, 0, 0);
+    };
+    auto blocks = [&](int64_t s0, auto n_c) {
       constexpr int NS = decltype(n_c)::value;
-      uint4 a[NS][MT], w[NS][NT][NB];
+      u32x4_t a[NS][2][MT], w[NS][NT][NB][2];
 #pragma unroll
       for (int u = 0; u < NS; ++u) {
-        const int64_t kbyte = (s0 + u) * 64;
+        const int64_t kbyte = (s0 + u) * 128;
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
           for (int b = 0; b < NB; ++b)
-            w[u][j][b] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4_t*>(b_base[j][b] + kbyte + b_off)));
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh)
+              w[u][j][b][hh] = load_w(b_base[j][b] + kbyte + (b_off + hh * b_half));
 #pragma unroll
         for (int i = 0; i < MT; ++i)
-          a[u][i] = (MT > 1 || a_on[i]) ? *reinterpret_cast<const uint4*>(a_base + kbyte + a_off[i])
-                                        : make_uint4(0, 0, 0, 0);
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh) a[u][hh][i] = load_a(i, kbyte + q4 * 32 + hh * 16);
       }
 #pragma unroll
       for (int u = 0; u < NS; ++u)
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
-          for (int j = 0; j < NT; ++j)
+          for (int b = 0; b < NB; ++b) {
+            u32x4_t w0, w1;
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-              acc[i][j][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  __builtin_bit_cast(bf16x8_t, a[u][i]), __builtin_bit_cast(bf16x8_t, w[u][j][b]),
-                  acc[i][j][b], 0, 0, 0);
+            for (int v = 0; v < 4; ++v) {
+              w0[v] = ror8_into(w[u][j][b][0][v], w[u][j][b][1][v], true);
+              w1[v] = ror8_into(w[u][j][b][1][v], w[u][j][b][0][v], false);
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+              mfma(acc[i][j][b], a[u][0][i], w0);
+              mfma(acc[i][j][b], a[u][1][i], w1);
+            }
+          }
     };
-    for (int64_t s0 = kb; s0 < kfull; s0 += U) steps(s0, std::integral_constant<int, U>{});
-    for (int64_t s0 = kfull; s0 < ke; ++s0) steps(s0, std::integral_constant<int, 1>{});
-    // the four waves' partial sums, RC row tiles at a time: every wave writes
-    // its own, then wave q adds up the (row tile, column tile) groups g with
-    // g % 4 == q and stores them. C layout of the 16x16 MFMA: lane holds
+    for (int64_t s0 = kb; s0 < kfull; s0 += U) blocks(s0, std::integral_constant<int, U>{});
+    for (int64_t s0 = kfull; s0 < ke; ++s0) blocks(s0, std::integral_constant<int, 1>{});
+    if (odd32) {
+      const int64_t kbyte = k64 * 128;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const u32x4_t w = load_w(b_base[j][b] + kbyte + b_off32);
+#pragma unroll
+          for (int i = 0; i < MT; ++i) mfma(acc[i][j][b], load_a(i, kbyte + q4 * 16), w);
+        }
+    }
+    // the waves' partial sums, RC row tiles at a time: every wave writes its
+    // own, then wave q adds up the (row tile, column tile) groups g with
+    // g % W == q and stores them. C layout of the 16x16 MFMA: lane holds
     // column (lane % 16), rows 4 * (lane / 16) + q of its 16-row tile.
 #pragma unroll
     for (int i0 = 0; i0 < MT; i0 += RC) {
@@ -439,7 +559,7 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
             for (int b = 0; b < NB; ++b) part[wave][ii][j][b][lane] = acc[i0 + ii][j][b];
       __syncthreads();
       const int groups = (MT - i0 < RC ? MT - i0 : RC) * NT;
-      for (int g = wave; g < groups; g += kSmallWaves) {
+      for (int g = wave; g < groups; g += W) {
         const int ii = g / NT, j = g % NT;
         const int64_t col = n0 + 16 * j + r;
         f32x4_t t[NB];
@@ -447,7 +567,7 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
         for (int b = 0; b < NB; ++b) {
           t[b] = part[0][ii][j][b][lane];
 #pragma unroll
-          for (int q = 1; q < kSmallWaves; ++q) t[b] += part[q][ii][j][b][lane];
+          for (int q = 1; q < W; ++q) t[b] += part[q][ii][j][b][lane];
         }
         if (col >= N_out) continue;
 #pragma unroll
@@ -461,15 +581,17 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
       __syncthreads();                             // part is rewritten next
     }
   };
-  // units (expert, column block) in list order, the grid striding over them:
+  // units (item, column block) in list order, the grid striding over them:
   // at any time the blocks work on neighbouring columns
   for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
-    const int e = small[1 + (int)(unit / ncb)];
+    const int32_t it = list[(int)(unit / ncb)];
+    const int e = it & 255;
     const int cb = (int)(unit % ncb);
-    int64_t lo = offsets[e], hi = offsets[e + 1];
-    lo = lo < 0 ? 0 : (lo > max_rows ? max_rows : lo);
-    hi = hi < lo ? lo : (hi > max_rows ? max_rows : hi);
-    const int m = (int)(hi - lo);                  // 1 .. 16 * MTMAX (the list's rule)
+    int64_t lo;
+    const int64_t rows = expert_rows(offsets, slot, e, S, max_rows, &lo);
+    const int64_t skip = (int64_t)(it >> 8) * kSmallRows;
+    lo += skip;
+    const int m = (int)min(rows - skip, (int64_t)kSmallRows);   // 1 .. 16 * MTMAX (the list's rule)
     const int mt = (m + 15) / 16;
     if (mt <= 1) run_unit(std::integral_constant<int, 1>{}, e, cb, m, lo);
     else if (mt == 2) { if constexpr (MTMAX >= 2) run_unit(std::integral_constant<int, 2>{}, e, cb, m, lo); }
@@ -1199,17 +1321,29 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
   // average): bf16, H and F multiples of 32 (the fast-path shapes), 32-bit lane
   // offsets within 96 rows of K. Larger batches leave the rare small expert to
   // the large tiles and launch no few-row kernel at all.
-  const int small_tiles =
-      fast && std::max(H, F) < ((int64_t)1 << 24) && max_rows <= 64 * (int64_t)E ? kSmallMaxTiles : 0;
-  ffn_tiles_kernel<<<dim3(1), dim3(64), 0, st>>>(expert_offsets, slot_of_expert, E, S, max_rows,
-                                                 bm, small_tiles, fast ? 1 : 0, prefix);
-  MOE_CHECK_LAUNCH();
-  const int32_t* const small = prefix + E + 1 + kCounterWords;
-  const int32_t* const prefix2 = small + E + 1;
-  const bool few = small_tiles > 0;
-  const bool big = max_rows > 16 * small_tiles;  // else every expert has few rows
-  // the most row tiles a listed expert can have, rounded up to a compiled bound
-  const int64_t few_tiles = std::min<int64_t>(ceil_div(max_rows, 16), small_tiles);
+  const bool few = fast && max_rows <= 64 * (int64_t)E;
+  const int small_tiles = few ? kSmallMaxTiles : 0;
+  // Whether an expert can hold more rows than one item decides if the large
+  // tiles are launched beside it. They cost the tile list and two launches
+  // that mostly find nothing (some 13 us); splitting such an expert into items
+  // costs reading its weights once more per item, some 9 us for 54 MB. At
+  // that size and below the few-row kernel takes every expert.
+  const int64_t extra = few ? (max_rows - 1) / kSmallRows : 0;
+  const bool only_few = few && extra <= kMaxExtraItems && extra * 6 * H * F <= 54 * 1000 * 1000;
+  const bool big = !only_few;
+  if (big) {
+    ffn_tiles_kernel<<<dim3(1), dim3(kMaxExperts), 0, st>>>(expert_offsets, slot_of_expert, E, S,
+                                                            max_rows, bm, small_tiles,
+                                                            fast ? 1 : 0, prefix);
+    MOE_CHECK_LAUNCH();
+  }
+  // without the large tiles the list (at most kMaxItems + 1 words) takes the
+  // place of their prefix and counters
+  int32_t* const small = only_few ? prefix : prefix + E + 1 + kCounterWords;
+  static_assert(kMaxItems + 1 <= kCounterWords, "the item list fits the counters' words");
+  const int32_t* const prefix2 = prefix + E + 1 + kCounterWords + E + 1;
+  // the most row tiles an item can have, rounded up to a compiled bound
+  const int64_t few_tiles = std::min<int64_t>(ceil_div(max_rows, 16), kSmallMaxTiles);
   const int mtmax = few_tiles <= 1 ? 1 : few_tiles <= 2 ? 2 : few_tiles <= 4 ? 4 : 6;
   int grid = device_cu_count();
   grid = std::min((grid + 7) / 8 * 8, kMaxTailTiles);     // a tail round has < grid tiles
@@ -1225,30 +1359,37 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
     float* const partial = reinterpret_cast<float*>(
         reinterpret_cast<char*>(prefix) + align_up((size_t)(E + 1 + kCounterWords + 2 * (E + 1)) * 4, 256));
     const int pieces = (int)max_split_pieces(max_rows, H, F, E);
-    // two blocks per compute unit, striding over the few-row experts' units
-    // (more blocks in flight spread the reads over more DRAM rows at once and
-    // measured slower; fewer leave bandwidth unused); with few units each
-    // block does one
-    auto small_grid = [&](int64_t n_out, int cols) {
-      return (unsigned)std::min<int64_t>(2 * (int64_t)device_cu_count(), (int64_t)E * ceil_div(n_out, cols));
+    // The few-row units: at most min(E, max_rows) + extra items. Two wide blocks
+    // or one narrow block per compute unit (8 waves either way) stride over
+    // them (more blocks in flight spread the reads over more DRAM rows at once
+    // and measured slower; fewer leave bandwidth unused). Narrow units where
+    // the wide ones are fewer than those blocks.
+    const int64_t items = std::min<int64_t>(E, max_rows) + extra;
+    const int64_t cus = device_cu_count();
+    auto launch_mt = [&](auto epi_c, auto narrow_c, auto mt_c, const uint16_t* a, int64_t K,
+                         const uint16_t* b0, const uint16_t* b1, uint16_t* c) {
+      constexpr int EPI = decltype(epi_c)::value;
+      constexpr bool NARROW = decltype(narrow_c)::value;
+      using SS = SmallShape<EPI, NARROW>;
+      const int64_t units = items * ceil_div(EPI == 0 ? F : H, SS::COLS);
+      const unsigned g = (unsigned)std::min<int64_t>((NARROW ? 1 : 2) * cus, units);
+      ffn_small_bf16<EPI, decltype(mt_c)::value, NARROW><<<dim3(g), dim3(64 * SS::WAVES), 0, st>>>(
+          a, K, b0, b1, F, H, expert_offsets, slot_of_expert, E, S, max_rows, only_few ? 1 : 0,
+          small, c);
+    };
+    auto launch_shape = [&](auto epi_c, auto narrow_c, const uint16_t* a, int64_t K,
+                            const uint16_t* b0, const uint16_t* b1, uint16_t* c) {
+      if (mtmax == 1) launch_mt(epi_c, narrow_c, std::integral_constant<int, 1>{}, a, K, b0, b1, c);
+      else if (mtmax == 2) launch_mt(epi_c, narrow_c, std::integral_constant<int, 2>{}, a, K, b0, b1, c);
+      else if (mtmax == 4) launch_mt(epi_c, narrow_c, std::integral_constant<int, 4>{}, a, K, b0, b1, c);
+      else launch_mt(epi_c, narrow_c, std::integral_constant<int, 6>{}, a, K, b0, b1, c);
     };
     auto launch_small = [&](auto epi_c, const uint16_t* a, int64_t K, const uint16_t* b0,
                             const uint16_t* b1, uint16_t* c) {
       constexpr int EPI = decltype(epi_c)::value;
-      const unsigned g = small_grid(EPI == 0 ? F : H, SmallShape<EPI>::COLS);
-      const dim3 blk(64 * kSmallWaves);
-      if (mtmax == 1)
-        ffn_small_bf16<EPI, 1><<<dim3(g), blk, 0, st>>>(a, K, b0, b1, F, H, expert_offsets,
-                                                        slot_of_expert, max_rows, small, c);
-      else if (mtmax == 2)
-        ffn_small_bf16<EPI, 2><<<dim3(g), blk, 0, st>>>(a, K, b0, b1, F, H, expert_offsets,
-                                                        slot_of_expert, max_rows, small, c);
-      else if (mtmax == 4)
-        ffn_small_bf16<EPI, 4><<<dim3(g), blk, 0, st>>>(a, K, b0, b1, F, H, expert_offsets,
-                                                        slot_of_expert, max_rows, small, c);
-      else
-        ffn_small_bf16<EPI, 6><<<dim3(g), blk, 0, st>>>(a, K, b0, b1, F, H, expert_offsets,
-                                                        slot_of_expert, max_rows, small, c);
+      const int64_t wide = items * ceil_div(EPI == 0 ? F : H, SmallShape<EPI, false>::COLS);
+      if (wide < 2 * cus) launch_shape(epi_c, std::true_type{}, a, K, b0, b1, c);
+      else launch_shape(epi_c, std::false_type{}, a, K, b0, b1, c);
     };
     if (big) {
       ffn_gemm_bf16_fast<0><<<dim3(grid), dim3(fast::kThreads), 0, st>>>(

@@ -95,6 +95,22 @@ def test_bf16_k_loop_edges(H, F):
     _run([290, 129, 70, 20, 256], H, F, None, 5, seed=H + F)
 
 
+@pytest.mark.parametrize("counts,H,F,slot", [
+    ([200, 97, 96, 5, 0, 1, 33, 17, 64, 80], 256, 512, None),   # experts of 3, 2 and 1 items
+    ([193, 0, 288, 2, 95, 1], 96, 160, None),        # K ends in 32 in both projections; 3 whole items
+    ([1, 0, 0, 2], 32, 2080, None),                  # K of one half block; more waves than K blocks
+    ([150, 7, 20, 100], 704, 96, [1, -1, 0, 2]),     # a split expert beside a missed one
+    ([1] * 256, 64, 64, None),                       # the longest list
+    ([40], 2048, 5632, None), ([2], 5632, 64, None),   # one expert: narrow units
+    ([3] * 60, 256, 1408, None),                     # narrow down, wide up
+])
+def test_bf16_few_row_items(counts, H, F, slot):
+    # decode-sized batches: no expert takes the large tiles, an expert of more
+    # than 96 rows is cut into items; bound of the other bf16 cases
+    S = len(counts) if slot is None else max(slot) + 1
+    _run(counts, H, F, slot, S, seed=sum(counts) + H, extra_rows=7)
+
+
 def test_bf16_resident_subset_and_slot_order():
     counts = [100, 200, 50, 300, 10, 0]
     slot = [2, -1, 0, -1, 1, 3]
