@@ -2,14 +2,13 @@
 // (the gating of Sec. 2.1 of the ExpertFlow paper).
 //
 // bf16 inputs: the projection z = x . W_g^T runs on MFMA (v_mfma_f32_16x16x32_bf16),
-// in float32 chains of 8 K-steps that are added into float64 accumulators.
-// Up to 32 and above 64 experts: 16 tokens per block, the K dimension split
-// into contiguous ranges over the waves. 33-64 experts: 16 to 64 tokens per
-// block in tiles of 16, the waves of a tile splitting the experts, the router
+// in float32 chains of 1 to 8 K-steps that are added into float64 accumulators.
+// Up to 32 and above 64 experts, and few tokens: 16 tokens per block, the K
+// dimension split into contiguous ranges over the waves. 33-64 experts: 16 to
+// 64 tokens per block in tiles of 16, the waves of a tile splitting the experts, the router
 // matrix staged through LDS chunk by chunk. The same block then selects the top-k of each token exactly (see
 // route_decide) and computes its gates.
-// float32 inputs (small, correctness-oriented): one block per token, one
-// thread per expert, float64 logits.
+// float32 inputs (small configurations): one block per token, float64 logits.
 #include "common.h"
 
 #include <math.h>
@@ -178,11 +177,6 @@ __device__ __forceinline__ void lds_wave_sync() {
 __device__ __forceinline__ uint4 abs_bf16x8(uint4 v) {
   return make_uint4(v.x & 0x7fff7fffu, v.y & 0x7fff7fffu, v.z & 0x7fff7fffu, v.w & 0x7fff7fffu);
 }
-
-// K-steps (of 32) accumulated in one float32 chain before it is added to the
-// float64 accumulator (the kernel for up to 32 or more than 64 experts; the
-// one for 33-64 experts closes chains of one or four K-steps).
-constexpr int kChainSteps = 8;
 
 // Exactness of the decision. A logit is an exact sum of exact bf16 products
 // (8-bit significands: every product is exact in float32). Each product passes
@@ -444,7 +438,9 @@ __device__ __forceinline__ void route_decide(const DecideLds<EP>& s, const uint1
 // Small or very large expert counts: 16 tokens per block, the K dimension
 // split into KS contiguous ranges, one per wave (each keeps up to 8 K-steps of
 // loads in flight). Partial sums are added in LDS in fixed wave order.
-template <int NEB, int KS>
+// U: K-steps of loads in flight; CH: K-steps per float32 chain; SLOT_KB: LDS
+// the per-wave partials may take.
+template <int NEB, int KS, int U, int CH, int SLOT_KB>
 __global__ void __launch_bounds__(KS * 64)
 route_ksplit_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int64_t T,
                     int64_t H, int E, int k, const float* __restrict__ bias, int bias_mode,
@@ -479,11 +475,10 @@ route_ksplit_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__
   const int64_t ksteps = (H + 31) / 32;
   const int64_t spw = (ksteps + KS - 1) / KS;     // K-steps per wave, contiguous
   const int64_t s_beg = wave * spw, s_end = min(ksteps, s_beg + spw);
-  constexpr int U = NEB >= 8 ? 1 : 8 / NEB;       // K-steps of loads in flight
-  for (int64_t s0 = s_beg; s0 < s_end; s0 += kChainSteps) {
-#pragma unroll
-    for (int nb = 0; nb < NEB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    const int64_t c_end = min(s_end, s0 + kChainSteps);
+  for (int64_t s0 = s_beg; s0 < s_end; s0 += U > CH ? U : CH) {
+    constexpr int R = U > CH ? U : CH;            // K-steps of a round
+    static_assert(R % U == 0 && R % CH == 0, "whole chains and load batches");
+    const int64_t c_end = min(s_end, s0 + R);
     for (int64_t s1 = s0; s1 < c_end; s1 += U) {
       uint4 a[U];
       uint4 b[U][NEB];
@@ -505,25 +500,30 @@ route_ksplit_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__
       for (int u = 0; u < U; ++u) {
         const bf16x8_t av = __builtin_bit_cast(bf16x8_t, a[u]);
         const bf16x8_t aa = __builtin_bit_cast(bf16x8_t, abs_bf16x8(a[u]));
+        const bool first = U >= CH ? u % CH == 0 : (s1 == s0 && u == 0);
+        const bool last = U >= CH ? (u + 1) % CH == 0 : (s1 + U >= c_end && u == U - 1);
 #pragma unroll
         for (int nb = 0; nb < NEB; ++nb) {
+          if (first) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
           acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               av, __builtin_bit_cast(bf16x8_t, b[u][nb]), acc[nb], 0, 0, 0);
           acs[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               aa, __builtin_bit_cast(bf16x8_t, abs_bf16x8(b[u][nb])), acs[nb], 0, 0, 0);
         }
+        if (last) {
+#pragma unroll
+          for (int nb = 0; nb < NEB; ++nb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a64[nb][i] += (double)acc[nb][i];
+        }
       }
     }
-#pragma unroll
-    for (int nb = 0; nb < NEB; ++nb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a64[nb][i] += (double)acc[nb][i];
   }
 
   // C layout of the 16x16 MFMA: lane holds column (lane % 16), rows
   // 4 * (lane / 16) + i. Wave partials are added in wave order: all at once
   // from per-wave slots when those fit in LDS, else one wave after another.
-  constexpr bool kSlots = KS * TB * EP * (sizeof(double) + sizeof(float)) <= 48 * 1024;
+  constexpr bool kSlots = KS * TB * EP * (sizeof(double) + sizeof(float)) <= SLOT_KB * 1024;
   if constexpr (kSlots) {
     __shared__ double zred[KS][TB][EP];
     __shared__ float sred[KS][TB][EP];
@@ -574,7 +574,7 @@ route_ksplit_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__
   if (threadIdx.x == 0) npairs = 0;
   __syncthreads();
   const DecideLds<EP> s{zf, sacc, zacc, sel, lk, need, pairs, &npairs};
-  route_decide<EP, TB, KS, kChainSteps>(s, x, wg, T, H, E, k, bias, bias_mode, renorm, tok0,
+  route_decide<EP, TB, KS, CH>(s, x, wg, T, H, E, k, bias, bias_mode, renorm, tok0,
                                         logits, topk_idx, topk_w);
 }
 
@@ -588,6 +588,11 @@ constexpr int kWPitch = kWChunk + 8;              // padded row (bank spread)
 // used (measured at 8192 Qwen-shaped tokens: 64-token tiles, 128 blocks, 59 us;
 // 32, 256 blocks, 46 us; 16, 512 blocks, 41 us)
 constexpr int kRouteTileBlocks = 2;
+// Up to one 16-token block per compute unit, 33-64 experts take the K-split
+// kernel: a block then waits for its chain of loads along K, which eight waves
+// walk in two steps each (Qwen shape, 24 tokens 18.5 -> 15.2 us, 4096 tokens
+// 25.2 -> 20.5). Beyond, its LDS (one block per compute unit) and the router
+// matrix read again per 16 tokens cost more (8192 tokens 31 -> 40 us).
 // float32 chain of the 33-64-expert kernel: one K-step while a wave holds one
 // or two 16-expert blocks, four for four blocks (one K-step there needs more
 // registers than the wave has)
@@ -737,24 +742,83 @@ route_f32_kernel(const float* __restrict__ x, const float* __restrict__ wg, int6
                  int64_t H, int E, int k, const float* __restrict__ bias, int bias_mode,
                  int renorm, float* __restrict__ logits, int32_t* __restrict__ topk_idx,
                  float* __restrict__ topk_w) {
+  // Each wave takes every fourth expert, its lanes splitting H; wave 0 then
+  // decides with four experts per lane. (One thread per expert walking H, and
+  // one thread deciding, took 12.6 us at H 128; 5.6 now, most of it launch and
+  // load latency.)
   __shared__ double z64[256];
-  __shared__ float z[256];
   const int64_t t = blockIdx.x;
-  const int e = threadIdx.x;
-  if (e < E) {
-    const float* xr = x + t * H;
-    const float* wr = wg + (int64_t)e * H;
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  const float* const xr = x + t * H;
+  for (int e = wave; e < E; e += 256 / kWave) {
+    const float* const wr = wg + (int64_t)e * H;
     double s = 0.0;
-    for (int64_t h = 0; h < H; ++h) s = fma((double)xr[h], (double)wr[h], s);
-    s += (double)bias_of(bias, bias_mode, t, E, e);
-    z64[e] = s;
-    z[e] = (float)s;
-    if (logits) logits[t * E + e] = (float)s;
+    for (int64_t h = lane; h < H; h += kWave) s = fma((double)xr[h], (double)wr[h], s);
+    s = wave_sum(s);
+    if (lane == 0) {
+      s += (double)bias_of(bias, bias_mode, t, E, e);
+      z64[e] = s;
+      if (logits) logits[t * E + e] = (float)s;
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    select_topk<double>(z64, E, k, nullptr, topk_idx + t * k);
-    gate_weights(z, E, k, renorm, topk_idx + t * k, topk_w + t * k);
+  if (wave != 0) return;
+  double v[4];
+  bool taken[4];
+  float mz = -INFINITY, total = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int e = lane + kWave * c;
+    taken[c] = e >= E;
+    v[c] = e < E ? z64[e] : 0.0;
+    if (e < E) mz = fmaxf(mz, (float)v[c]);
+  }
+  for (int o = 32; o > 0; o >>= 1) mz = fmaxf(mz, __shfl_xor(mz, o, kWave));
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (lane + kWave * c < E) total += expf((float)v[c] - mz);
+  total = wave_sum(total);
+  // k rounds of arg-max (larger value, then lower id); lane j keeps round j's
+  // winner (rounds past 63 in further registers)
+  int win[4] = {0, 0, 0, 0};
+  float ev[4] = {0.f, 0.f, 0.f, 0.f};
+  float sel = 0.f;
+  for (int j = 0; j < k; ++j) {
+    double bv = 0.0;
+    int be = -1;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (!taken[c] && (be < 0 || v[c] > bv)) {
+        bv = v[c];
+        be = lane + kWave * c;
+      }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double ov = __shfl_xor(bv, o, kWave);
+      const int oe = __shfl_xor(be, o, kWave);
+      if (oe >= 0 && (be < 0 || ov > bv || (ov == bv && oe < be))) {
+        bv = ov;
+        be = oe;
+      }
+    }
+    const float g = expf((float)bv - mz);
+    sel += g;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (lane + kWave * c == be) taken[c] = true;
+      if (j == lane + kWave * c) {
+        win[c] = be;
+        ev[c] = g;
+      }
+    }
+  }
+  const float den = renorm ? sel : total;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int j = lane + kWave * c;
+    if (j < k) {
+      topk_idx[t * k + j] = win[c];
+      topk_w[t * k + j] = ev[c] / den;
+    }
   }
 }
 
@@ -844,6 +908,14 @@ extern "C" int moe_route(const void* x, const void* w_gate, int32_t dtype, int64
   const int neb = (E + 15) / 16;
   const auto* xb = static_cast<const uint16_t*>(x);
   const auto* wb = static_cast<const uint16_t*>(w_gate);
+#define MOE_ROUTE_LAUNCH(N, W, U, CH, KB)                                                 \
+  route_ksplit_kernel<N, W, U, CH, KB><<<dim3((unsigned)blocks), dim3(W * 64), 0, st>>>(  \
+      xb, wb, T, H, E, k, bias, bias_mode, renormalize, logits, topk_idx, topk_w)
+  if ((neb == 3 || neb == 4) && blocks <= device_cu_count()) {
+    MOE_ROUTE_LAUNCH(4, 8, 4, 1, 100);
+    MOE_CHECK_LAUNCH();
+    return MOE_OK;
+  }
   if (neb == 3 || neb == 4) {
     // the largest token tile that still gives every compute unit kRouteTileBlocks blocks
     const int64_t cus = device_cu_count();
@@ -863,13 +935,10 @@ extern "C" int moe_route(const void* x, const void* w_gate, int32_t dtype, int64
     MOE_CHECK_LAUNCH();
     return MOE_OK;
   }
-#define MOE_ROUTE_LAUNCH(N, W)                                                            \
-  route_ksplit_kernel<N, W><<<dim3((unsigned)blocks), dim3(W * 64), 0, st>>>(             \
-      xb, wb, T, H, E, k, bias, bias_mode, renormalize, logits, topk_idx, topk_w)
-  if (neb <= 1) MOE_ROUTE_LAUNCH(1, 8);
-  else if (neb <= 2) MOE_ROUTE_LAUNCH(2, 8);
-  else if (neb <= 8) MOE_ROUTE_LAUNCH(8, 4);
-  else MOE_ROUTE_LAUNCH(16, 4);
+  if (neb <= 1) MOE_ROUTE_LAUNCH(1, 8, 8, 1, 48);
+  else if (neb <= 2) MOE_ROUTE_LAUNCH(2, 8, 4, 1, 48);
+  else if (neb <= 8) MOE_ROUTE_LAUNCH(8, 4, 1, 8, 48);
+  else MOE_ROUTE_LAUNCH(16, 4, 1, 8, 48);
 #undef MOE_ROUTE_LAUNCH
   MOE_CHECK_LAUNCH();
   return MOE_OK;

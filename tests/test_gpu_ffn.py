@@ -111,6 +111,18 @@ def test_bf16_few_row_items(counts, H, F, slot):
     _run(counts, H, F, slot, S, seed=sum(counts) + H, extra_rows=7)
 
 
+@pytest.mark.parametrize("counts,H,F,slot", [
+    ([1, 0, 64, 65, 130], 128, 256, None),           # row groups of 64: whole, one over, several
+    ([20, 3, 17], 4, 20, [1, -1, 0]),                # the shortest K, a part of a column block, a miss
+    ([70, 33], 68, 36, None),                        # K ends inside a 16-wide step
+    ([5, 40], 30, 50, None),                         # rows not 16-byte aligned: one thread per output
+    ([1] * 130, 16, 16, None),                       # experts past the first 64 and 128
+])
+def test_f32_groups(counts, H, F, slot):
+    S = len(counts) if slot is None else max(slot) + 1
+    _run(counts, H, F, slot, S, seed=sum(counts) + H, dtype="f32", tol=1e-4, extra_rows=3)
+
+
 def test_bf16_resident_subset_and_slot_order():
     counts = [100, 200, 50, 300, 10, 0]
     slot = [2, -1, 0, -1, 1, 3]

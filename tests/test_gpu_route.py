@@ -159,3 +159,33 @@ def test_x_mode_crafted_ties_60_experts(T):
     # seven strong experts compete for four places: the crafted pairs are
     # decided in a large share of the tokens
     assert (got == 12).any(axis=1).mean() > 0.4 and (got == 59).any(axis=1).mean() > 0.4
+
+
+def test_x_mode_crafted_ties_16_token_tiles():
+    # more 16-token blocks than compute units: the tile kernel with 16-token
+    # tiles (fewer take the K-split kernel, the 64-token case above)
+    test_x_mode_crafted_ties_60_experts(5000)
+
+
+@pytest.mark.parametrize("T,H,E,k,bias_kind", [
+    (5, 100, 200, 70, None), (3, 64, 256, 256, "token"), (9, 7, 5, 5, "expert"), (2, 130, 65, 1, None),
+])
+def test_f32_router(T, H, E, k, bias_kind):
+    """float32 inputs are decided in float64: exact ties (equal router rows)
+    go to the lower id at any rank; gates within float32 rounding."""
+    g = np.random.default_rng(31 + E)
+    x = g.standard_normal((T, H)).astype(np.float32)
+    w = (g.standard_normal((E, H)) * 0.2).astype(np.float32)
+    w[E // 2] = w[1]
+    w[E - 1] = w[1]
+    bias = None if bias_kind is None else \
+        g.standard_normal((T, E) if bias_kind == "token" else E).astype(np.float32)
+    z = x.astype(np.float64) @ w.astype(np.float64).T + (0.0 if bias is None else bias)
+    for renorm in (True, False):
+        idx, gate, lg = ops.route(to_dev(x), to_dev(w), k, want_logits=True, renormalize=renorm,
+                                  bias=None if bias is None else to_dev(bias))
+        ref = oracle.topk_select(z, k)
+        assert np.array_equal(to_host(idx), ref)
+        # a float32 exponential of a float32 difference, summed over E
+        assert np.max(np.abs(to_host(gate) - oracle.gate_weights(z, ref, renorm))) <= 1e-5
+        assert np.max(np.abs(to_host(lg) - z)) <= 2.0 ** -23 * np.max(np.abs(z))
