@@ -1,8 +1,10 @@
 // Forward pass of the routing path predictor (Sec. 3.2): a T5-style
 // encoder-decoder whose L heads give every token logits over the E experts of
 // each MoE layer, and their sigmoids as activation probabilities (B, S, L, E).
-// Everything is float32: on gfx950 the float32 matrix and vector peaks are the
-// same, so the contractions (hidden size 32) run as LDS-tiled vector GEMMs.
+// Everything is float32. Hidden size 32 (the paper's) runs on float32 MFMAs,
+// with everything between two attentions in one kernel per block of rows
+// (rpp_rows32) and, for heads of 8, attention on MFMAs too (rpp_attention8);
+// other sizes run as LDS-tiled vector kernels, one per step.
 #include "moeflow.h"
 #include "common.h"
 
@@ -246,6 +248,347 @@ rpp_attention(const float* __restrict__ Q, int64_t ldq, const float* __restrict_
   for (int c = 0; c < DK; ++c) O[(base + i) * ldo + h * DK + c] = acc[c] * inv;
 }
 
+// The same for heads of 8 on float32 MFMAs (16x16x4). A wave owns 16 queries and
+// walks the keys 64 at a time: scores^T = K . Q^T puts 4 x 4 keys of one query
+// in each lane (query lane % 16, keys 16 t + 4 (lane / 16) + v), and that is the
+// operand layout of O^T = V^T . P^T, so the probabilities go from one product
+// into the next in registers. The running maximum is common to a query's four
+// lanes (two shuffles per 64 keys), the sums are merged at the end. The vector
+// form spent four 16-byte LDS reads and some thirty vector operations per
+// (query, key) pair: 34.8 us at 16 x 512 tokens.
+template <bool BIAS>
+__global__ void __launch_bounds__(256)
+rpp_attention8(const float* __restrict__ Q, int64_t ldq, const float* __restrict__ Kp,
+               const float* __restrict__ Vp, int64_t ldkv, int S, int h_count,
+               const float* __restrict__ rel, RelBuckets rb, int causal, float* __restrict__ O,
+               int64_t ldo) {
+  constexpr int DK = 8;
+  extern __shared__ __attribute__((aligned(16))) float att_lds[];
+  const int S64 = (S + 63) / 64 * 64;
+  const int vp = S64 + 4;                            // pitch of a V^T row
+  float* const ks = att_lds;                         // [S64][8]
+  float* const vt = ks + (size_t)S64 * DK;           // [8][vp]
+  float* const bt = vt + (size_t)DK * vp;            // bias of distance n at bt[n + S - 1]
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int64_t base = (int64_t)b * S;
+  for (int q = threadIdx.x; q < S64 * DK; q += blockDim.x) {
+    const int j = q / DK, c = q % DK;
+    const bool in = j < S;                           // keys past the end: zeros, masked below
+    ks[q] = in ? Kp[(base + j) * ldkv + h * DK + c] : 0.f;
+    vt[c * vp + j] = in ? Vp[(base + j) * ldkv + h * DK + c] : 0.f;
+  }
+  if (BIAS)
+    for (int q = threadIdx.x; q < 2 * S - 1; q += blockDim.x)
+      bt[q] = rel[rel_bucket(rb, q - (S - 1)) * h_count + h];
+  __syncthreads();
+  const int lane = lane_id();
+  const int i0 = (blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * 16;
+  if (i0 >= S) return;
+  const int r = lane & 15, q4 = lane >> 4;
+  const int i = min(i0 + r, S - 1);                  // queries past the end repeat the last
+  const float* const qrow = Q + (base + i) * ldq + h * DK;
+  const float q0 = qrow[2 * q4], q1 = qrow[2 * q4 + 1];
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};                // O^T: rows 0-7 are the head's columns
+  float mx = -INFINITY, den = 0.f;
+  const int jend = causal ? min(S, i0 + 16) : S;
+  for (int j0 = 0; j0 < jend; j0 += 64) {
+    f32x4_t sc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float2 kk = *reinterpret_cast<const float2*>(ks + (j0 + 16 * t + r) * DK + 2 * q4);
+      sc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kk.x, q0, sc[t], 0, 0, 0);
+      sc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kk.y, q1, sc[t], 0, 0, 0);
+    }
+    const bool edge = j0 + 64 > S || (causal && j0 + 63 > i0);   // wave-uniform
+    float m = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int j = j0 + 16 * t + 4 * q4 + v;
+        if (BIAS) sc[t][v] += bt[max(i - j, 1 - S) + S - 1];
+        if (edge && (j >= S || (causal && j > i))) sc[t][v] = -INFINITY;
+        m = fmaxf(m, sc[t][v]);
+      }
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    const float nm = fmaxf(mx, m);                   // finite: key 0 is never masked
+    const float scale = __expf(mx - nm);
+    mx = nm;
+    den *= scale;
+    // the block's own sum first: chains of 64 products, then one per 64 keys
+    f32x4_t blk = {0.f, 0.f, 0.f, 0.f};
+    float dblk = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float4 vv = *reinterpret_cast<const float4*>(vt + (r & 7) * vp + j0 + 16 * t + 4 * q4);
+      const float va[4] = {vv.x, vv.y, vv.z, vv.w};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float p = __expf(sc[t][v] - nm);
+        dblk += p;
+        blk = __builtin_amdgcn_mfma_f32_16x16x4f32(va[v], p, blk, 0, 0, 0);
+      }
+    }
+    den += dblk;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = fmaf(acc[v], scale, blk[v]);
+  }
+  den += __shfl_xor(den, 16);
+  den += __shfl_xor(den, 32);
+  if (q4 >= 2 || i0 + r >= S) return;                // O^T rows 4 q4 + v, columns queries
+  const float inv = 1.0f / den;
+  float* const o = O + (base + i) * ldo + h * DK + 4 * q4;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) o[v] = acc[v] * inv;
+}
+
+// ---------------------------------------------------------- rows of width 32
+// Everything a row of hidden size 32 goes through between two attentions, in
+// one kernel over 16 * RT rows a block: the attention's output projection and
+// residual, RMS norm, and either
+//   kRowsCross  the cross-attention's query and its keys and values (from the
+//               encoder output), or
+//   kRowsMlp    the feed-forward block with its residual, the next RMS norm and
+//               the next query/key/value projection (or, after a stack, the
+//               normalised rows alone);
+//   kRowsEmbed  starts a stack: embedding, norm, query/key/value.
+// All products are float32 MFMAs (16x16x4) computed transposed, out^T = W .
+// rows^T: a lane loads 16 bytes of a weight row and of a row of x (4
+// neighbouring k, one for each of four MFMAs), and the result, 4 neighbouring
+// outputs of one row per lane, is both a 16-byte store and the operand layout
+// of the next product, so the feed-forward's hidden units stay in registers.
+// Its width is dealt to the waves 16 units at a time, the partial sums are
+// added in wave order. What bounds it: the MFMAs of the feed-forward (14 us of
+// a 16 x 512 token batch at the float32 peak); as vector kernels, with the
+// products around it in 11 launches per layer, the feed-forward alone took 104.
+constexpr int kRowsEmbed = 0, kRowsCross = 1, kRowsMlp = 2;
+
+struct Rows32 {
+  int64_t M;
+  float eps;
+  const int32_t* ids;                  // embed
+  const float* emb;
+  int vocab;
+  int32_t* err;
+  float* x;                            // the residual stream [M, 32]
+  const float* o;                      // attention output [M, 32]
+  const float* wout;                   // its projection [32, 32]
+  const float* ln;                     // the norm after it (embed: the only one)
+  const float *w1, *w2;                // feed-forward [dff, 32], [32, dff]
+  int dff;
+  const float* ln_next;                // the norm after the feed-forward
+  const float* wnext;                  // projection of the normalised rows [n_next, 32]
+  int n_next;                          // 0: store the normalised rows
+  float* next;                         // [M, n_next] or [M, 32]
+  const float* enc;                    // cross: encoder output, wkv [64, 32] -> kv [M, 64]
+  const float* wkv;
+  float* kv;
+};
+
+template <int MODE, int RT, int NW>
+__global__ void __launch_bounds__(64 * NW)
+rpp_rows32(Rows32 a) {
+  constexpr int R = 16 * RT, D = 32, P = D + 4;      // pitch: 16-byte rows, spread over banks
+  __shared__ __attribute__((aligned(16))) float xs[R][P], ns[R][P];
+  __shared__ __attribute__((aligned(16))) float part[MODE == kRowsMlp ? NW : 1][R][P];
+  const int tid = threadIdx.x;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int c16 = lane & 15, q4 = lane >> 4;
+  const int64_t r0 = (int64_t)blockIdx.x * R;
+  auto row_at = [&](int r) { return min(r0 + r, a.M - 1); };   // rows past M repeat the last
+
+  // B operand of 16 rows: lane (row c16, q4) holds k = 16 s + 4 q4 + v at [4 s + v]
+  auto rows_of = [&](const float* p, float (&f)[8]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const float4 u = *reinterpret_cast<const float4*>(p + 16 * s + 4 * q4);
+      f[4 * s] = u.x;
+      f[4 * s + 1] = u.y;
+      f[4 * s + 2] = u.z;
+      f[4 * s + 3] = u.w;
+    }
+  };
+  // 16 outputs (weight rows w, row stride D) of those 16 rows
+  auto product = [&](const float* w, const float (&f)[8]) {
+    float g[8];
+    rows_of(w + (int64_t)c16 * D, g);
+    f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) d = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k], f[k], d, 0, 0, 0);
+    return d;
+  };
+  // ns = rms(xs) * w, 64 NW / R threads a row
+  auto norm = [&](const float* w) {
+    constexpr int TPR = 64 * NW / R, PER = D / TPR;
+    static_assert(TPR <= 32 && PER >= 1, "threads per row");
+    const int r = tid / TPR, c = tid % TPR * PER;
+    float v[PER], ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      v[j] = xs[r][c + j];
+      ss += v[j] * v[j];
+    }
+#pragma unroll
+    for (int o = TPR / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    const float inv = 1.0f / sqrtf(ss / (float)D + a.eps);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) ns[r][c + j] = v[j] * inv * w[c + j];
+  };
+  // out[row, 0..n) = ns . w^T, the 16 x 16 tiles dealt to the waves
+  auto project = [&](const float* w, int n, float* out) {
+    const int tiles = (n / 16) * RT;
+    for (int t = wave; t < tiles; t += NW) {
+      const int rt = t % RT, ot = t / RT;
+      float f[8];
+      rows_of(&ns[16 * rt + c16][0], f);
+      const f32x4_t d = product(w + (int64_t)ot * 16 * D, f);
+      const int64_t row = r0 + 16 * rt + c16;
+      if (row < a.M) *reinterpret_cast<f32x4_t*>(out + row * n + 16 * ot + 4 * q4) = d;
+    }
+  };
+
+  if constexpr (MODE == kRowsEmbed) {
+    for (int q = tid; q < R * D; q += 64 * NW) {
+      const int r = q / D, c = q % D;
+      const int id = a.ids[row_at(r)];
+      const bool ok = id >= 0 && id < a.vocab;
+      if (!ok && c == 0 && r0 + r < a.M) atomicExch(a.err, 1);
+      const float v = ok ? a.emb[(int64_t)id * D + c] : 0.f;
+      xs[r][c] = v;
+      if (r0 + r < a.M) a.x[(r0 + r) * D + c] = v;
+    }
+    __syncthreads();
+    norm(a.ln);
+    __syncthreads();
+    project(a.wnext, a.n_next, a.next);
+    return;
+  }
+
+  for (int t = wave; t < 2 * RT; t += NW) {          // x += o . wout^T
+    const int rt = t % RT, ot = t / RT;
+    const int64_t row = row_at(16 * rt + c16);
+    float f[8];
+    rows_of(a.o + row * D, f);
+    const float4 xo = *reinterpret_cast<const float4*>(a.x + row * D + 16 * ot + 4 * q4);
+    const f32x4_t d = product(a.wout + (int64_t)ot * 16 * D, f);
+    *reinterpret_cast<float4*>(&xs[16 * rt + c16][16 * ot + 4 * q4]) =
+        make_float4(xo.x + d[0], xo.y + d[1], xo.z + d[2], xo.w + d[3]);
+  }
+  __syncthreads();
+  norm(a.ln);
+  __syncthreads();
+  auto store_x = [&]() {
+    for (int q = tid; q < R * D / 4; q += 64 * NW) {
+      const int r = q / (D / 4), c = q % (D / 4) * 4;
+      if (r0 + r < a.M)
+        *reinterpret_cast<float4*>(a.x + (r0 + r) * D + c) = *reinterpret_cast<const float4*>(&xs[r][c]);
+    }
+  };
+  if constexpr (MODE == kRowsCross) {
+    store_x();
+    project(a.wnext, a.n_next, a.next);
+    for (int t = wave; t < 4 * RT; t += NW) {        // kv = enc . wkv^T
+      const int rt = t % RT, ot = t / RT;
+      const int64_t row = r0 + 16 * rt + c16;
+      float f[8];
+      rows_of(a.enc + row_at(16 * rt + c16) * D, f);
+      const f32x4_t d = product(a.wkv + (int64_t)ot * 16 * D, f);
+      if (row < a.M) *reinterpret_cast<f32x4_t*>(a.kv + row * 64 + 16 * ot + 4 * q4) = d;
+    }
+    return;
+  }
+  // feed-forward: hidden units 16 c .. 16 c + 15 of chunk c, chunks dealt to the
+  // waves; the next chunk's weights load while this one's products run
+  float f[RT][8];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) rows_of(&ns[16 * rt + c16][0], f[rt]);
+  // sums in two levels, kSumChunks chunks (128 products) a chain: no longer
+  // chains, so no larger rounding error, than the vector kernels' parts of 256
+  constexpr int kSumChunks = 8;
+  f32x4_t acc[RT][2], sum[RT][2];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot) acc[rt][ot] = sum[rt][ot] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int chunks = (a.dff + 15) / 16;
+  f32x4_t w1[2], w2[2];
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  auto fetch = [&](int c, f32x4_t (&u1)[2], f32x4_t (&u2)[2]) {
+    const int h1 = 16 * c + c16, h2 = 16 * c + 4 * q4;         // dff is a multiple of 4
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      u1[s] = h1 < a.dff ? *reinterpret_cast<const f32x4_t*>(a.w1 + (int64_t)h1 * D + 16 * s + 4 * q4) : zero;
+      u2[s] = h2 < a.dff ? *reinterpret_cast<const f32x4_t*>(a.w2 + (int64_t)(16 * s + c16) * a.dff + h2) : zero;
+    }
+  };
+  if (wave < chunks) fetch(wave, w1, w2);
+  int in_chain = 0;
+  for (int c = wave; c < chunks; c += NW) {
+    if (in_chain++ == kSumChunks) {
+      in_chain = 1;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot) {
+          sum[rt][ot] += acc[rt][ot];
+          acc[rt][ot] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    f32x4_t n1[2] = {zero, zero}, n2[2] = {zero, zero};
+    if (c + NW < chunks) fetch(c + NW, n1, n2);
+    f32x4_t hid[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) hid[rt] = zero;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+        hid[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[k / 4][k % 4], f[rt][k], hid[rt], 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const float hv = fmaxf(hid[rt][v], 0.f);
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot)
+          acc[rt][ot] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[ot][v], hv, acc[rt][ot], 0, 0, 0);
+      }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      w1[s] = n1[s];
+      w2[s] = n2[s];
+    }
+  }
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot)
+      *reinterpret_cast<f32x4_t*>(&part[MODE == kRowsMlp ? wave : 0][16 * rt + c16][16 * ot + 4 * q4]) =
+          sum[rt][ot] + acc[rt][ot];
+  __syncthreads();
+  for (int q = tid; q < R * D; q += 64 * NW) {
+    const int r = q / D, c = q % D;
+    float v = part[0][r][c];
+#pragma unroll
+    for (int w = 1; w < (MODE == kRowsMlp ? NW : 1); ++w) v += part[w][r][c];
+    xs[r][c] += v;
+  }
+  __syncthreads();
+  norm(a.ln_next);
+  store_x();
+  __syncthreads();
+  if (a.n_next > 0) {
+    project(a.wnext, a.n_next, a.next);
+  } else {
+    for (int q = tid; q < R * D; q += 64 * NW) {
+      const int r = q / D, c = q % D;
+      if (r0 + r < a.M) a.next[(r0 + r) * D + c] = ns[r][c];
+    }
+  }
+}
+
 constexpr int kMlpRows = 32, kMlpChunk = 64, kMlpSplit = 8;   // fused feed-forward tiles
 
 struct RppOffsets {
@@ -444,11 +787,31 @@ int mlp(hipStream_t st, const float* n, int64_t M, int d, const float* W1, const
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+template <int MODE>
+int rows32(hipStream_t st, const Rows32& a) {
+  // 16 rows and 8 waves a block while that leaves a compute unit no more than
+  // one, else 32 rows and 4 waves, which read the weights half as often
+  const int64_t b16 = ceil_div(a.M, 16);
+  if (b16 <= device_cu_count()) rpp_rows32<MODE, 1, 8><<<dim3((unsigned)b16), dim3(512), 0, st>>>(a);
+  else rpp_rows32<MODE, 2, 4><<<dim3((unsigned)ceil_div(a.M, 32)), dim3(256), 0, st>>>(a);
+  return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 int attention(hipStream_t st, int dk, const float* Q, int64_t ldq, const float* Kp,
               const float* Vp, int64_t ldkv, int B, int S, int h, const float* rel,
               const RelBuckets& rb, bool use_bias, bool causal, float* O, int64_t ldo) {
   const dim3 grid((unsigned)ceil_div(S, kAttQ), (unsigned)h, (unsigned)B);
   const size_t lds = ((size_t)2 * S * dk + 2 * S) * sizeof(float);
+  const size_t lds8 = ((size_t)ceil_div(S, 64) * 64 * 16 + 32 + 2 * (size_t)S) * sizeof(float);
+  if (dk == 8 && lds8 <= 64 * 1024) {                // padded keys still fit
+    if (use_bias)
+      rpp_attention8<true><<<grid, dim3(256), lds8, st>>>(Q, ldq, Kp, Vp, ldkv, S, h, rel, rb,
+                                                          causal ? 1 : 0, O, ldo);
+    else
+      rpp_attention8<false><<<grid, dim3(256), lds8, st>>>(Q, ldq, Kp, Vp, ldkv, S, h, rel, rb,
+                                                           causal ? 1 : 0, O, ldo);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+  }
 #define MOE_ATT(DKV)                                                                          \
   rpp_attention<DKV><<<grid, dim3(kAttQ * kSplit), lds, st>>>(                               \
       Q, ldq, Kp, Vp, ldkv, S, h, rel, rb, use_bias ? 1 : 0, causal ? 1 : 0, O, ldo)
@@ -511,6 +874,75 @@ extern "C" int moe_rpp_forward(const int32_t* ids, int32_t B, int32_t S, const m
     rc = (expr);                      \
     if (rc != MOE_OK) return rc;      \
   } while (0)
+
+  // Hidden size 32: one launch per attention and one for all between two of
+  // them. Needs a layer on each side, and 16-byte aligned weight rows.
+  if (d == 32 && g.n_enc >= 1 && g.n_dec >= 1 && g.d_ff % 4 == 0 &&
+      ((size_t)g.num_buckets * h) % 4 == 0 && (reinterpret_cast<uintptr_t>(weights) & 15) == 0) {
+    Rows32 a{};
+    a.M = M;
+    a.eps = g.eps;
+    a.ids = ids;
+    a.emb = W + wo.emb;
+    a.vocab = g.vocab;
+    a.err = err;
+    a.o = o;
+    a.dff = g.d_ff;
+    auto embed = [&](float* stream_x, const float* layer) {
+      a.x = stream_x;
+      a.ln = layer;
+      a.wnext = layer + d;
+      a.n_next = 3 * d;
+      a.next = qkv;
+      return rows32<kRowsEmbed>(st, a);
+    };
+    // feed-forward at p (norm, W1, W2), then the next layer's first norm and
+    // projection, or the stack's last norm into `last`
+    auto feed_forward = [&](const float* wout, const float* p, const float* next_layer,
+                            const float* ln_last, float* last) {
+      a.wout = wout;
+      a.ln = p;
+      a.w1 = p + d;
+      a.w2 = a.w1 + df;
+      a.ln_next = next_layer ? next_layer : ln_last;
+      a.wnext = next_layer ? next_layer + d : nullptr;
+      a.n_next = next_layer ? 3 * d : 0;
+      a.next = next_layer ? qkv : last;
+      return rows32<kRowsMlp>(st, a);
+    };
+    MOE_RC(embed(x, W + wo.enc[0]));
+    for (int l = 0; l < g.n_enc; ++l) {
+      const float* const wout = W + wo.enc[l] + d + 3 * dd;
+      MOE_RC(attention(st, dk, qkv, 3 * d, qkv + d, qkv + 2 * d, 3 * d, B, S, h, W + wo.enc_rel,
+                       rb_enc, true, false, o, d));
+      MOE_RC(feed_forward(wout, wout + dd, l + 1 < g.n_enc ? W + wo.enc[l + 1] : nullptr,
+                          W + wo.enc_ln, enc));
+    }
+    MOE_RC(embed(y, W + wo.dec[0]));
+    for (int l = 0; l < g.n_dec; ++l) {
+      const float* const wout = W + wo.dec[l] + d + 3 * dd;
+      const float* const ln2 = wout + dd;
+      const float *cq = ln2 + d, *ckv = cq + dd, *cout = ckv + 2 * dd;
+      MOE_RC(attention(st, dk, qkv, 3 * d, qkv + d, qkv + 2 * d, 3 * d, B, S, h, W + wo.dec_rel,
+                       rb_dec, true, true, o, d));
+      a.wout = wout;
+      a.ln = ln2;
+      a.wnext = cq;
+      a.n_next = d;
+      a.next = qkv;
+      a.enc = enc;
+      a.wkv = ckv;
+      a.kv = kv;
+      MOE_RC(rows32<kRowsCross>(st, a));
+      MOE_RC(attention(st, dk, qkv, d, kv, kv + d, 2 * d, B, S, h, nullptr, rb_dec, false, false,
+                       o, d));
+      MOE_RC(feed_forward(cout, cout + dd, l + 1 < g.n_dec ? W + wo.dec[l + 1] : nullptr,
+                          W + wo.dec_ln, n));
+    }
+    MOE_RC(gemm<G_SIGMOID>(st, n, d, W + wo.heads, M, (int64_t)g.L * g.E, d, lg,
+                           (int64_t)g.L * g.E, probs));
+    return MOE_OK;
+  }
 
   rpp_embed<<<dim3((unsigned)ceil_div(M * d, 256)), dim3(256), 0, st>>>(ids, M, g.vocab, d,
                                                                       W + wo.emb, x, err);

@@ -129,3 +129,35 @@ def test_other_widths(d, h):
     # d = 64: the fused feed-forward's widest tile; d = 24: two GEMMs through memory
     dims = dict(PAPER, vocab=300, d_model=d, n_heads=h, d_ff=200, n_enc=2, n_dec=1, L=3, E=7)
     _check(dims, 3, 45, seed=20 + d)
+
+
+@pytest.mark.parametrize("B,S,over", [
+    (1, 1, {}), (2, 15, {}), (1, 16, {}), (3, 17, {}),       # one wave's queries and rows
+    (2, 63, dict(d_ff=36)), (1, 64, dict(d_ff=4)), (1, 65, dict(d_ff=500)),   # key blocks; part of a chunk
+    (33, 129, dict(d_ff=64)),                   # 4257 rows: 32 a block, the last one short
+    (1, 910, dict(d_ff=64, n_enc=1, n_dec=1)),  # keys padded to 64 no longer fit LDS
+    (2, 40, dict(d_ff=50)), (2, 40, dict(num_buckets=34, max_distance=128, n_heads=1)),
+])
+def test_width_32_edges(B, S, over):
+    # float32 sums of at most 2048 terms, as the other cases; num_buckets 34 is
+    # refused (its halves are no powers of two), d_ff 50 takes the general kernels
+    dims = dict(PAPER, vocab=300, L=3, E=7, **over)
+    if dims["num_buckets"] == 34:
+        with pytest.raises(ops.MoeError):
+            _check(dims, B, S, seed=70)
+        return
+    _check(dims, B, S, seed=70 + S)
+
+
+def test_width_32_unaligned_weights():
+    # weights one float past a 16-byte boundary take the general kernels
+    dims = dict(PAPER, vocab=100, d_ff=64, L=2, E=4)
+    w = to_dev(_weights(dims, 8))
+    buf = torch.empty(w.numel() + 1, device=w.device)
+    buf[1:] = w
+    ids = to_dev(np.arange(60, dtype=np.int32).reshape(2, 30))
+    p0, l0, _ = ops.rpp_forward(ids, w, dims, want_logits=True)
+    p1, l1, _ = ops.rpp_forward(ids, buf[1:], dims, want_logits=True)
+    torch.cuda.synchronize()
+    assert (l0 - l1).abs().max() <= 1e-4 * l0.abs().max() + 1e-5
+    assert (p0 - p1).abs().max() <= 1e-5
