@@ -256,8 +256,9 @@ rpp_attention(const float* __restrict__ Q, int64_t ldq, const float* __restrict_
 // lanes (two shuffles per 64 keys), the sums are merged at the end. The vector
 // form spent four 16-byte LDS reads and some thirty vector operations per
 // (query, key) pair: 34.8 us at 16 x 512 tokens.
+constexpr int kAtt8Threads = 512, kAtt8Q = kAtt8Threads / kWave * 16;   // queries per block
 template <bool BIAS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kAtt8Threads)
 rpp_attention8(const float* __restrict__ Q, int64_t ldq, const float* __restrict__ Kp,
                const float* __restrict__ Vp, int64_t ldkv, int S, int h_count,
                const float* __restrict__ rel, RelBuckets rb, int causal, float* __restrict__ O,
@@ -271,18 +272,28 @@ rpp_attention8(const float* __restrict__ Q, int64_t ldq, const float* __restrict
   float* const bt = vt + (size_t)DK * vp;            // bias of distance n at bt[n + S - 1]
   const int h = blockIdx.y, b = blockIdx.z;
   const int64_t base = (int64_t)b * S;
-  for (int q = threadIdx.x; q < S64 * DK; q += blockDim.x) {
-    const int j = q / DK, c = q % DK;
-    const bool in = j < S;                           // keys past the end: zeros, masked below
-    ks[q] = in ? Kp[(base + j) * ldkv + h * DK + c] : 0.f;
-    vt[c * vp + j] = in ? Vp[(base + j) * ldkv + h * DK + c] : 0.f;
+  // half rows of 16 bytes (row strides and head offsets are multiples of 4
+  // floats); keys past the end: zeros, masked below
+#pragma unroll 2
+  for (int q = threadIdx.x; q < S64 * 2; q += kAtt8Threads) {
+    const int j = q >> 1, c = (q & 1) * 4;
+    float4 kk = make_float4(0.f, 0.f, 0.f, 0.f), vv = kk;
+    if (j < S) {
+      kk = *reinterpret_cast<const float4*>(Kp + (base + j) * ldkv + h * DK + c);
+      vv = *reinterpret_cast<const float4*>(Vp + (base + j) * ldkv + h * DK + c);
+    }
+    *reinterpret_cast<float4*>(ks + j * DK + c) = kk;
+    vt[c * vp + j] = vv.x;
+    vt[(c + 1) * vp + j] = vv.y;
+    vt[(c + 2) * vp + j] = vv.z;
+    vt[(c + 3) * vp + j] = vv.w;
   }
   if (BIAS)
-    for (int q = threadIdx.x; q < 2 * S - 1; q += blockDim.x)
+    for (int q = threadIdx.x; q < 2 * S - 1; q += kAtt8Threads)
       bt[q] = rel[rel_bucket(rb, q - (S - 1)) * h_count + h];
   __syncthreads();
   const int lane = lane_id();
-  const int i0 = (blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * 16;
+  const int i0 = blockIdx.x * kAtt8Q + threadIdx.x / kWave * 16;
   if (i0 >= S) return;
   const int r = lane & 15, q4 = lane >> 4;
   const int i = min(i0 + r, S - 1);                  // queries past the end repeat the last
@@ -789,11 +800,11 @@ int mlp(hipStream_t st, const float* n, int64_t M, int d, const float* W1, const
 
 template <int MODE>
 int rows32(hipStream_t st, const Rows32& a) {
-  // 16 rows and 8 waves a block while that leaves a compute unit no more than
-  // one, else 32 rows and 4 waves, which read the weights half as often
+  // 16 rows a block while that leaves a compute unit no more than one block,
+  // else 32 rows, which read the weights half as often
   const int64_t b16 = ceil_div(a.M, 16);
   if (b16 <= device_cu_count()) rpp_rows32<MODE, 1, 8><<<dim3((unsigned)b16), dim3(512), 0, st>>>(a);
-  else rpp_rows32<MODE, 2, 4><<<dim3((unsigned)ceil_div(a.M, 32)), dim3(256), 0, st>>>(a);
+  else rpp_rows32<MODE, 2, 8><<<dim3((unsigned)ceil_div(a.M, 32)), dim3(512), 0, st>>>(a);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -804,12 +815,13 @@ int attention(hipStream_t st, int dk, const float* Q, int64_t ldq, const float* 
   const size_t lds = ((size_t)2 * S * dk + 2 * S) * sizeof(float);
   const size_t lds8 = ((size_t)ceil_div(S, 64) * 64 * 16 + 32 + 2 * (size_t)S) * sizeof(float);
   if (dk == 8 && lds8 <= 64 * 1024) {                // padded keys still fit
+    const dim3 grid8((unsigned)ceil_div(S, kAtt8Q), (unsigned)h, (unsigned)B);
     if (use_bias)
-      rpp_attention8<true><<<grid, dim3(256), lds8, st>>>(Q, ldq, Kp, Vp, ldkv, S, h, rel, rb,
-                                                          causal ? 1 : 0, O, ldo);
+      rpp_attention8<true><<<grid8, dim3(kAtt8Threads), lds8, st>>>(
+          Q, ldq, Kp, Vp, ldkv, S, h, rel, rb, causal ? 1 : 0, O, ldo);
     else
-      rpp_attention8<false><<<grid, dim3(256), lds8, st>>>(Q, ldq, Kp, Vp, ldkv, S, h, rel, rb,
-                                                           causal ? 1 : 0, O, ldo);
+      rpp_attention8<false><<<grid8, dim3(kAtt8Threads), lds8, st>>>(
+          Q, ldq, Kp, Vp, ldkv, S, h, rel, rb, causal ? 1 : 0, O, ldo);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
   }
 #define MOE_ATT(DKV)                                                                          \
