@@ -1272,9 +1272,10 @@ static_assert(kSmallN <= (1 << kSmallRankBits), "rank field");
 static_assert((int64_t)kSmallN * 2 * kSmallMaxLk <= (1ll << (32 - kSmallRankBits)), "sum field");
 
 // The nodes of one launch: block b splits the n[b] tokens at perm[lo[b] ...]
-// with n1[b] in batch 1 and writes info row row[b].
+// with n1[b] in batch 1 and writes info row row[b] and, from row batch[b] on,
+// the demand of its two halves (batch[b] < 0: of neither).
 struct SmallNodes {
-  int32_t lo[kSmallBatch], n[kSmallBatch], n1[kSmallBatch], row[kSmallBatch];
+  int32_t lo[kSmallBatch], n[kSmallBatch], n1[kSmallBatch], row[kSmallBatch], batch[kSmallBatch];
 };
 
 struct SmallLds {
@@ -1380,18 +1381,22 @@ __device__ __forceinline__ int small_block_scan(int v, int* total, int* red) {
 // the node-local index of the token at position j of the split (batch 1, then
 // batch 2, each ascending). ids_in == 1: token i is routes row perm[lo + i],
 // and the same positions receive those row ids (the node's tokens reordered
-// in place). demand (single node only) and info may be null.
+// in place). demand and info may be null.
 __global__ void __launch_bounds__(kSel)
 sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in, int L, int E,
           int k, int W, int max_iters, int keep, int nbins, int32_t* __restrict__ perm,
-          int32_t* __restrict__ demand, int64_t* __restrict__ info_rows) {
+          int32_t* __restrict__ demand_rows, int64_t* __restrict__ info_rows) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_lds[];
   __shared__ uint32_t s_red[2 * kSel / kWave];
   __shared__ int s_t, s_below;
   const int tid = threadIdx.x;
   const int N = nodes.n[blockIdx.x], n1 = nodes.n1[blockIdx.x], lo = nodes.lo[blockIdx.x];
   int64_t* const info = info_rows ? info_rows + 8 * (int64_t)nodes.row[blockIdx.x] : nullptr;
+  int32_t* const demand = demand_rows && nodes.batch[blockIdx.x] >= 0
+                              ? demand_rows + (int64_t)nodes.batch[blockIdx.x] * L * E : nullptr;
   if (N == 0) {                                  // an empty node: nothing to split
+    if (demand)
+      for (int c = tid; c < 2 * L * E; c += kSel) demand[c] = 0;
     if (info && tid < 8) info[tid] = (tid == 1) ? 1 : (tid == 2 || tid == 3) ? -1 : 0;
     return;
   }
@@ -1419,10 +1424,7 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
   if (tid < N) gid[tid] = my_id;
 
   for (int q = tid; q < 2 * NW; q += kSel) bits32[q] = 0;
-  for (int c = tid; c < LE; c += kSel) {
-    cnt_all[c] = 0;
-    cnt_orig[c] = 0;
-  }
+  for (int c = tid; c < LE; c += kSel) cnt_all[c] = 0;
   for (int i = tid; i < N; i += kSel) {
     ones[i] = 0;
     sall[i] = 0;
@@ -1439,9 +1441,9 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
     const uint32_t m = 1u << (col & 31);
     if (atomicOr(&bits32[tok * 2 * W + (col >> 5)], m) & m) return;
     ++my_ones;
-    atomicAdd(&ones[tok], 1);
-    atomicAdd(&cnt_all[col], 1);
-    if (tok < n1) atomicAdd(&cnt_orig[col], 1);
+    // both counts of a column (at most kSmallN each) in one word until the
+    // paths are complete
+    atomicAdd(&cnt_all[col], tok < n1 ? 0x10001 : 1);
   };
   // 16-byte pieces when rows allow it: the node's rows back to back (ids_in
   // == 0), or whole rows of 16-byte multiples (ids_in == 1); else bytes
@@ -1494,6 +1496,16 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
   }
   int tot_all = 0;
   (void)small_block_scan(my_ones, &tot_all, s_redi);  // its barriers publish bits and counts
+  for (int c = tid; c < LE; c += kSel) {
+    const int both = cnt_all[c];
+    cnt_orig[c] = both >> 16;
+    cnt_all[c] = both & 0xffff;
+  }
+  for (int q = tid; q < NW; q += kSel) {         // |r_i|
+    const int c = __popcll(bits[q]);
+    if (c) atomicAdd(&ones[q / W], c);
+  }
+  __syncthreads();
 
   // per token: sum over its columns of cnt[]; accumulated into out[] (zeroed)
   auto col_sums = [&](const int* cnt, int* out) {
@@ -2003,12 +2015,12 @@ constexpr int32_t kMaxMultiBatches = 4096;
 
 struct MultiNode {
   int64_t lo, n;
-  int32_t b, depth;
+  int32_t b, depth, batch;       // batch: the node's first batch
 };
 
 // Nodes of the recursion in pre-order (sizes depend on N and B only).
 std::vector<MultiNode> multi_nodes(int64_t N, int32_t B) {
-  std::vector<MultiNode> out, stack{{0, N, B, 0}};
+  std::vector<MultiNode> out, stack{{0, N, B, 0, 0}};
   while (!stack.empty()) {
     const MultiNode v = stack.back();
     stack.pop_back();
@@ -2016,29 +2028,10 @@ std::vector<MultiNode> multi_nodes(int64_t N, int32_t B) {
     out.push_back(v);
     const int32_t bl = v.b / 2;
     const int64_t n1 = v.n * bl / v.b;
-    stack.push_back({v.lo + n1, v.n - n1, v.b - bl, v.depth + 1});   // right after left
-    stack.push_back({v.lo, n1, bl, v.depth + 1});
+    stack.push_back({v.lo + n1, v.n - n1, v.b - bl, v.depth + 1, v.batch + bl});   // right after left
+    stack.push_back({v.lo, n1, bl, v.depth + 1, v.batch});
   }
   return out;
-}
-
-// Batch boundaries on the host (the device kernel below computes the same).
-std::vector<int64_t> multi_offsets_host(int64_t N, int32_t B) {
-  std::vector<int64_t> off{0};
-  std::vector<std::pair<int64_t, int32_t>> stack{{N, B}};
-  while (!stack.empty()) {
-    const auto v = stack.back();
-    stack.pop_back();
-    if (v.second == 1) {
-      off.push_back(off.back() + v.first);
-      continue;
-    }
-    const int32_t bl = v.second / 2;
-    const int64_t n1 = v.first * bl / v.second;
-    stack.push_back({v.first - n1, v.second - bl});
-    stack.push_back({n1, bl});
-  }
-  return off;
 }
 
 struct MultiLayout {
@@ -2131,7 +2124,7 @@ __global__ void sch_multi_zero(int64_t n, int32_t* __restrict__ p) {
 // counts kDemandChunk tokens of batch b into an LDS histogram when L*E fits
 // (else straight into memory), then adds it to demand (zeroed first): many
 // blocks per batch keep the LDS atomics on the few (l, e) cells of small E
-// from serialising. A token repeating an expert within a layer counts once.
+// from serialising. Only for a single batch: a split knows its halves' counts. A token repeating an expert within a layer counts once.
 constexpr int kDemandLdsWords = 16384;
 constexpr int kDemandChunk = 256;
 template <bool LDS>
@@ -2208,8 +2201,29 @@ extern "C" int moe_schedule_multi(const uint8_t* routes, int64_t N, int32_t L, i
   const int64_t row = (int64_t)L * k;
   if (ceil_div(N * row, 256) > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
 
-  sch_multi_iota<<<dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, st>>>(N, perm);
-  MOE_CHECK_LAUNCH();
+  // A split leaves the demand of its halves in two rows from the node's first
+  // batch on: those are batches when the node has two, the left one is when it
+  // has three (the other row is then rewritten by the child's split, later on
+  // the stream).
+  const int64_t LE = (int64_t)L * E;
+  if (demand && ceil_div((int64_t)B * LE, 256) > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
+  auto demand_batch = [&](const MultiNode& v) { return v.b <= 3 ? v.batch : -1; };
+  auto demand_of = [&](const MultiNode& v) -> int32_t* {
+    return demand && demand_batch(v) >= 0 ? demand + v.batch * LE : nullptr;
+  };
+  // The root holds every token in index order: the two-way scheduler on the
+  // caller's routes, straight into perm (gathering, composing and counting
+  // again were six launches, 36 us of 153 at 8192 tokens).
+  const std::vector<MultiNode> nodes = multi_nodes(N, B);
+  if (nodes.empty()) {
+    sch_multi_iota<<<dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, st>>>(N, perm);
+    MOE_CHECK_LAUNCH();
+  } else {
+    const int rc = moe_schedule(routes, N, L, E, k, N * (B / 2) / B, max_iters,
+                                keep_original_if_worse, perm, demand_of(nodes[0]),
+                                info ? info : info_scratch, err_out, sub_ws, sub_bytes, stream);
+    if (rc != MOE_OK) return rc;
+  }
   // one node through the general two-way path: its routes gathered, split,
   // its range of perm composed with the split's order
   auto multi_split = [&](const MultiNode& v, size_t q) -> int {
@@ -2220,7 +2234,7 @@ extern "C" int moe_schedule_multi(const uint8_t* routes, int64_t N, int32_t L, i
         routes, ids, v.n, row, rt);
     MOE_CHECK_LAUNCH();
     const int rc = moe_schedule(rt, v.n, L, E, k, n1, max_iters, keep_original_if_worse, sub_perm,
-                                nullptr, info_row, err_out, sub_ws, sub_bytes, stream);
+                                demand_of(v), info_row, err_out, sub_ws, sub_bytes, stream);
     if (rc != MOE_OK) return rc;
     const dim3 g((unsigned)ceil_div(v.n, 256));
     sch_multi_compose<<<g, dim3(256), 0, st>>>(ids, sub_perm, v.n, tmp);
@@ -2233,17 +2247,16 @@ extern "C" int moe_schedule_multi(const uint8_t* routes, int64_t N, int32_t L, i
   // on its parent: a level's nodes that fit the one-block path run as one
   // launch (a block per node, tokens reordered in place), the others one
   // after another.
-  const std::vector<MultiNode> nodes = multi_nodes(N, B);
   int32_t depth_max = 0;
   for (const MultiNode& v : nodes) depth_max = std::max(depth_max, v.depth);
-  for (int32_t d = 0; d <= depth_max && !nodes.empty(); ++d) {
+  for (int32_t d = 1; d <= depth_max; ++d) {
     SmallNodes tab{};
     int count = 0;
     size_t lds = 0;
     auto flush = [&]() -> int {
       if (count == 0) return MOE_OK;
       if (small_launch(routes, tab, count, 1, L, E, k, max_iters, keep_original_if_worse, lds,
-                       perm, nullptr, info, st) != hipSuccess)
+                       perm, demand, info, st) != hipSuccess)
         return MOE_ERR_HIP;
       count = 0;
       lds = 0;
@@ -2257,6 +2270,7 @@ extern "C" int moe_schedule_multi(const uint8_t* routes, int64_t N, int32_t L, i
         tab.n[count] = (int32_t)v.n;
         tab.n1[count] = (int32_t)(v.n * (v.b / 2) / v.b);
         tab.row[count] = (int32_t)q;
+        tab.batch[count] = demand_batch(v);
         lds = std::max(lds, b);
         if (++count == kSmallBatch) {
           const int rc = flush();
@@ -2264,7 +2278,11 @@ extern "C" int moe_schedule_multi(const uint8_t* routes, int64_t N, int32_t L, i
         }
         continue;
       }
-      if (v.n == 0) {                            // an empty node: its info row only
+      if (v.n == 0) {                            // an empty node: its info and demand rows
+        if (int32_t* const rows = demand_of(v)) {
+          sch_multi_zero<<<dim3((unsigned)ceil_div(2 * LE, 256)), dim3(256), 0, st>>>(2 * LE, rows);
+          MOE_CHECK_LAUNCH();
+        }
         if (info) {
           sch_multi_info_empty<<<dim3(1), dim3(64), 0, st>>>(info + 8 * (int64_t)q);
           MOE_CHECK_LAUNCH();
@@ -2280,17 +2298,10 @@ extern "C" int moe_schedule_multi(const uint8_t* routes, int64_t N, int32_t L, i
   sch_multi_offsets<<<dim3((unsigned)ceil_div(B + 1, 256)), dim3(256), 0, st>>>(N, B,
                                                                               batch_offsets);
   MOE_CHECK_LAUNCH();
-  if (demand) {
-    const int64_t LE = (int64_t)L * E;
-    const int64_t cells = (int64_t)B * LE;
-    if (ceil_div(cells, 256) > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
-    sch_multi_zero<<<dim3((unsigned)ceil_div(cells, 256)), dim3(256), 0, st>>>(cells, demand);
+  if (demand && B == 1) {
+    sch_multi_zero<<<dim3((unsigned)ceil_div(LE, 256)), dim3(256), 0, st>>>(LE, demand);
     MOE_CHECK_LAUNCH();
-    // chunks of the largest batch (sizes depend on N and B only)
-    const std::vector<int64_t> off = multi_offsets_host(N, B);
-    int64_t largest = 0;
-    for (int32_t j = 0; j < B; ++j) largest = std::max(largest, off[j + 1] - off[j]);
-    const dim3 g((unsigned)std::max<int64_t>(1, ceil_div(largest, kDemandChunk)), (unsigned)B);
+    const dim3 g((unsigned)ceil_div(N, kDemandChunk));
     if (LE <= kDemandLdsWords)
       sch_multi_demand<true><<<g, dim3(256), 0, st>>>(routes, perm, batch_offsets, L, E, k,
                                                        demand);
