@@ -365,26 +365,29 @@ ffn_gemm_bf16(const uint16_t* __restrict__ A, int64_t K,
 // instruction a register), which leaves two MFMA operands: lane (row r, q)
 // holds the 16-byte chunk 2q of the row's line in the first and 2q + 1 in the
 // second, and the activation rows are read in the same order.
-// Two shapes. WIDE, 4 waves and four 16-column weight tiles a unit (32 columns
-// of gate and of up, or 64 of down): fewest activation loads per weight byte.
-// NARROW, 8 waves and one 16-column tile (of gate and of up, or of down): four
-// times the blocks and twice the waves, for launches of so few units that wide
-// ones would leave compute units without work (one expert of width 5632 has
-// 32 wide units in its down projection, 128 narrow ones).
+// Three shapes. kWide, 4 waves and four 16-column weight tiles a unit (32
+// columns of gate and of up, or 64 of down): fewest activation loads per weight
+// byte, two blocks per compute unit. kMid, the same unit with 8 waves, for
+// launches whose wide units are no more than the compute units. kNarrow, 8 waves
+// and one 16-column tile (of gate and of up, or of down), where those are no
+// more than the compute units either (one expert of width 5632 has 32 wide
+// units in its down projection, 128 narrow ones).
 constexpr int kSmallRC = 2;                      // row tiles per LDS reduction pass
 
-template <int EPI, bool NARROW>
+constexpr int kWide = 0, kMid = 1, kNarrow = 2;
+
+template <int EPI, int SHAPE>
 struct SmallShape {
   static constexpr int NB = EPI == 0 ? 2 : 1;    // gate and up, or down
-  static constexpr int NT = NARROW ? 1 : 4 / NB; // 16-column MFMA tiles per unit
+  static constexpr int NT = SHAPE == kNarrow ? 1 : 4 / NB;   // 16-column MFMA tiles per unit
   static constexpr int COLS = 16 * NT;
-  static constexpr int WAVES = NARROW ? 8 : 4;
+  static constexpr int WAVES = SHAPE == kWide ? 4 : 8;
 };
 
 // K blocks of 64 loaded per batch: as many as the registers hold beside the
 // accumulators
-template <int MT, bool NARROW>
-constexpr int small_unroll() { return (MT <= 2 ? 2 : 1) * (NARROW ? 2 : 1); }
+template <int MT, int SHAPE>
+constexpr int small_unroll() { return (MT <= 2 ? 2 : 1) * (SHAPE == kNarrow ? 2 : 1); }
 
 __device__ __forceinline__ uint32_t ror8_into(uint32_t keep, uint32_t from, bool high) {
   // lanes 8..15 (high) or 0..7 of each row of 16 take `from` of the lane 8 away
@@ -397,14 +400,14 @@ __device__ __forceinline__ uint32_t ror8_into(uint32_t keep, uint32_t from, bool
 // build: the list is made here, by every block for itself (and left in `small`
 // by block 0 for the down projection), instead of coming from the tile-list
 // kernel: saves that launch where nothing needs the large tiles.
-template <int EPI, int MTMAX, bool NARROW>
-__global__ void __launch_bounds__(NARROW ? 512 : 256) __attribute__((amdgpu_waves_per_eu(2)))
+template <int EPI, int MTMAX, int SHAPE>
+__global__ void __launch_bounds__(SHAPE == kWide ? 256 : 512) __attribute__((amdgpu_waves_per_eu(2)))
 ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __restrict__ B0,
                const uint16_t* __restrict__ B1, int64_t F, int64_t H,
                const int32_t* __restrict__ offsets, const int32_t* __restrict__ slot, int E, int S,
                int64_t max_rows, int build, int32_t* __restrict__ small,
                uint16_t* __restrict__ C) {
-  using SS = SmallShape<EPI, NARROW>;
+  using SS = SmallShape<EPI, SHAPE>;
   constexpr int NB = SS::NB, NT = SS::NT, W = SS::WAVES;
   constexpr int RC = MTMAX < kSmallRC ? MTMAX : kSmallRC;
   __shared__ f32x4_t part[W][RC][NT][NB][kWave];
@@ -449,7 +452,7 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
   const uint32_t b_half = (uint32_t)(8 * K * 2);       // the tile's rows 8 to 15
   auto run_unit = [&](auto mt_c, int e, int cb, int m, int64_t lo) {
     constexpr int MT = decltype(mt_c)::value;
-    constexpr int U = small_unroll<MT, NARROW>();
+    constexpr int U = small_unroll<MT, SHAPE>();
     const int s = slot ? slot[e] : e;
     const int64_t kfull = kb + (ke - kb) / U * U;
     const int64_t n0 = (int64_t)cb * SS::COLS;
@@ -1486,36 +1489,38 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
         reinterpret_cast<char*>(prefix) + align_up((size_t)(E + 1 + kCounterWords + 2 * (E + 1)) * 4, 256));
     const int pieces = (int)max_split_pieces(max_rows, H, F, E);
     // The few-row units: at most min(E, max_rows) + extra items. Two wide blocks
-    // or one narrow block per compute unit (8 waves either way) stride over
-    // them (more blocks in flight spread the reads over more DRAM rows at once
-    // and measured slower; fewer leave bandwidth unused). Narrow units where
-    // the wide ones are fewer than those blocks.
+    // or one block of 8 waves per compute unit stride over them (more blocks in
+    // flight spread the reads over more DRAM rows at once and measured slower;
+    // fewer leave bandwidth unused).
     const int64_t items = std::min<int64_t>(E, max_rows) + extra;
     const int64_t cus = device_cu_count();
-    auto launch_mt = [&](auto epi_c, auto narrow_c, auto mt_c, const uint16_t* a, int64_t K,
+    auto launch_mt = [&](auto epi_c, auto shape_c, auto mt_c, const uint16_t* a, int64_t K,
                          const uint16_t* b0, const uint16_t* b1, uint16_t* c) {
-      constexpr int EPI = decltype(epi_c)::value;
-      constexpr bool NARROW = decltype(narrow_c)::value;
-      using SS = SmallShape<EPI, NARROW>;
+      constexpr int EPI = decltype(epi_c)::value, SHAPE = decltype(shape_c)::value;
+      using SS = SmallShape<EPI, SHAPE>;
       const int64_t units = items * ceil_div(EPI == 0 ? F : H, SS::COLS);
-      const unsigned g = (unsigned)std::min<int64_t>((NARROW ? 1 : 2) * cus, units);
-      ffn_small_bf16<EPI, decltype(mt_c)::value, NARROW><<<dim3(g), dim3(64 * SS::WAVES), 0, st>>>(
+      const unsigned g = (unsigned)std::min<int64_t>((SHAPE == kWide ? 2 : 1) * cus, units);
+      ffn_small_bf16<EPI, decltype(mt_c)::value, SHAPE><<<dim3(g), dim3(64 * SS::WAVES), 0, st>>>(
           a, K, b0, b1, F, H, expert_offsets, slot_of_expert, E, S, max_rows, only_few ? 1 : 0,
           small, c);
     };
-    auto launch_shape = [&](auto epi_c, auto narrow_c, const uint16_t* a, int64_t K,
+    auto launch_shape = [&](auto epi_c, auto shape_c, const uint16_t* a, int64_t K,
                             const uint16_t* b0, const uint16_t* b1, uint16_t* c) {
-      if (mtmax == 1) launch_mt(epi_c, narrow_c, std::integral_constant<int, 1>{}, a, K, b0, b1, c);
-      else if (mtmax == 2) launch_mt(epi_c, narrow_c, std::integral_constant<int, 2>{}, a, K, b0, b1, c);
-      else if (mtmax == 4) launch_mt(epi_c, narrow_c, std::integral_constant<int, 4>{}, a, K, b0, b1, c);
-      else launch_mt(epi_c, narrow_c, std::integral_constant<int, 6>{}, a, K, b0, b1, c);
+      if (mtmax == 1) launch_mt(epi_c, shape_c, std::integral_constant<int, 1>{}, a, K, b0, b1, c);
+      else if (mtmax == 2) launch_mt(epi_c, shape_c, std::integral_constant<int, 2>{}, a, K, b0, b1, c);
+      else if (mtmax == 4) launch_mt(epi_c, shape_c, std::integral_constant<int, 4>{}, a, K, b0, b1, c);
+      else launch_mt(epi_c, shape_c, std::integral_constant<int, 6>{}, a, K, b0, b1, c);
     };
     auto launch_small = [&](auto epi_c, const uint16_t* a, int64_t K, const uint16_t* b0,
                             const uint16_t* b1, uint16_t* c) {
       constexpr int EPI = decltype(epi_c)::value;
-      const int64_t wide = items * ceil_div(EPI == 0 ? F : H, SmallShape<EPI, false>::COLS);
-      if (wide < 2 * cus) launch_shape(epi_c, std::true_type{}, a, K, b0, b1, c);
-      else launch_shape(epi_c, std::false_type{}, a, K, b0, b1, c);
+      const int64_t n_out = EPI == 0 ? F : H;
+      if (items * ceil_div(n_out, SmallShape<EPI, kNarrow>::COLS) <= cus)
+        launch_shape(epi_c, std::integral_constant<int, kNarrow>{}, a, K, b0, b1, c);
+      else if (items * ceil_div(n_out, SmallShape<EPI, kMid>::COLS) <= cus)
+        launch_shape(epi_c, std::integral_constant<int, kMid>{}, a, K, b0, b1, c);
+      else
+        launch_shape(epi_c, std::integral_constant<int, kWide>{}, a, K, b0, b1, c);
     };
     if (big) {
       ffn_gemm_bf16_fast<0><<<dim3(grid), dim3(fast::kThreads), 0, st>>>(

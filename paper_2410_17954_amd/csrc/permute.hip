@@ -1,8 +1,8 @@
 // moe_permute: stable expert-major grouping of (token, choice) pairs and the
 // gather of hidden-state rows into that order.
 //
-// Three launches, all on the caller's stream, over chunks of ct consecutive
-// batch tokens (ct * k pairs):
+// Up to three launches, all on the caller's stream, over chunks of ct
+// consecutive batch tokens (ct * k pairs); few pairs take only the last:
 //   1. count          -- one block per chunk counts the experts of its pairs in
 //                        an LDS histogram;
 //   2. column scan    -- one block per expert turns that expert's counts over
@@ -140,12 +140,18 @@ __device__ int block_excl_scan_lds(int v, int* total) {
 }
 
 // Rows are moved as 16-byte vectors; row_vecs = row bytes / 16 (0: maps only).
-// SUM_COUNTS: the block sums the per-chunk counts itself (few chunks x
-// experts); otherwise chunk_base/totals come from perm_colscan_kernel.
+// SRC kSumCounts: the block sums the per-chunk counts itself (few chunks x
+// experts); kScanned: chunk_base/totals come from perm_colscan_kernel;
+// kOwnCounts: the block counts the experts of all pairs itself, and no other
+// kernel runs (few pairs: every block reads their ids once more, from L2, for
+// a launch less; 5 us of a decode step's 13 for this path).
 // Global loads are issued in dependency order -- counts, the experts of the
 // first 256 pairs, then the chunk's first rows of x -- and the ranking
 // synchronises through LDS only, so the row reads overlap all index work.
-template <bool SUM_COUNTS>
+constexpr int kScanned = 0, kSumCounts = 1, kOwnCounts = 2;
+constexpr int kOwnRounds = 8;                    // pairs per thread in kOwnCounts
+constexpr int64_t kOwnPairs = (int64_t)kOwnRounds * kPermThreads;
+template <int SRC>
 __global__ void __launch_bounds__(kPermThreads)
 perm_rank_gather_kernel(PairSrc src, int64_t T, int64_t ct, int64_t nchunks,
                         const int32_t* __restrict__ counts, const int32_t* __restrict__ chunk_base,
@@ -172,7 +178,15 @@ perm_rank_gather_kernel(PairSrc src, int64_t T, int64_t ct, int64_t nchunks,
   int32_t all = 0, bef = 0;
   const int G = kPermThreads / E;
   const int g = tid / E, ge = tid - g * E;
-  if (SUM_COUNTS) {
+  int e_all[SRC == kOwnCounts ? kOwnRounds : 1];
+  if (SRC == kOwnCounts) {
+    const int64_t P = T * k;
+#pragma unroll
+    for (int u = 0; u < kOwnRounds; ++u) {
+      const int64_t p = (int64_t)u * kPermThreads + tid;
+      e_all[SRC == kOwnCounts ? u : 0] = p < P ? pair_expert(src, p) : -1;
+    }
+  } else if (SRC == kSumCounts) {
     if (g < G) {
       // eight loads in flight per round
       int64_t cq = g;
@@ -240,7 +254,15 @@ perm_rank_gather_kernel(PairSrc src, int64_t T, int64_t ct, int64_t nchunks,
     for (int w = 0; w < kWaves; ++w) wave_cnt[w][e] = 0;
   }
   lds_sync();
-  if (SUM_COUNTS) {
+  if (SRC == kOwnCounts) {
+#pragma unroll
+    for (int u = 0; u < kOwnRounds; ++u) {
+      const int e = e_all[SRC == kOwnCounts ? u : 0];
+      if (e < 0) continue;
+      atomicAdd(&tot[e], 1);
+      if ((int64_t)u * kPermThreads + tid < p0) atomicAdd(&base[e], 1);
+    }
+  } else if (SRC == kSumCounts) {
     if (g < G) {
       atomicAdd(&tot[ge], all);
       atomicAdd(&base[ge], bef);
@@ -354,20 +376,27 @@ int permute_run(const void* x, int32_t dtype, int64_t H, int64_t n_tokens,
   int32_t* chunk_base = counts + nchunks * E;
   int32_t* totals = chunk_base + nchunks * E;
   PairSrc src{token_ids, topk_idx, n_tokens, k, E};
+  if (P <= kOwnPairs) {
+    perm_rank_gather_kernel<kOwnCounts><<<dim3((unsigned)nchunks), dim3(kPermThreads), 0, st>>>(
+        src, T, ct, nchunks, nullptr, nullptr, nullptr, expert_offsets, row_of_pair, pair_of_row,
+        static_cast<const uint4*>(x), row_vecs, static_cast<uint4*>(x_perm));
+    MOE_CHECK_LAUNCH();
+    return MOE_OK;
+  }
   perm_count_kernel<<<dim3((unsigned)nchunks), dim3(kPermThreads), 0, st>>>(src, P, ct * k, counts);
   MOE_CHECK_LAUNCH();
   // Few (chunk, expert) counts: every block sums them itself; otherwise one
   // more launch scans them per expert.
   const bool sum_in_block = nchunks * E <= kSumInBlockCounts;
   if (sum_in_block) {
-    perm_rank_gather_kernel<true><<<dim3((unsigned)nchunks), dim3(kPermThreads), 0, st>>>(
+    perm_rank_gather_kernel<kSumCounts><<<dim3((unsigned)nchunks), dim3(kPermThreads), 0, st>>>(
         src, T, ct, nchunks, counts, nullptr, nullptr, expert_offsets, row_of_pair, pair_of_row,
         static_cast<const uint4*>(x), row_vecs, static_cast<uint4*>(x_perm));
   } else {
     perm_colscan_kernel<<<dim3((unsigned)E), dim3(kPermThreads), 0, st>>>(counts, nchunks, E,
                                                                          chunk_base, totals);
     MOE_CHECK_LAUNCH();
-    perm_rank_gather_kernel<false><<<dim3((unsigned)nchunks), dim3(kPermThreads), 0, st>>>(
+    perm_rank_gather_kernel<kScanned><<<dim3((unsigned)nchunks), dim3(kPermThreads), 0, st>>>(
         src, T, ct, nchunks, counts, chunk_base, totals, expert_offsets, row_of_pair,
         pair_of_row, static_cast<const uint4*>(x), row_vecs, static_cast<uint4*>(x_perm));
   }

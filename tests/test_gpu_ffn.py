@@ -123,6 +123,15 @@ def test_f32_groups(counts, H, F, slot):
     _run(counts, H, F, slot, S, seed=sum(counts) + H, dtype="f32", tol=1e-4, extra_rows=3)
 
 
+@pytest.mark.parametrize("counts,H,F", [
+    ([129, 192, 193, 224, 225], 256, 512),     # edges of the one-tile modes
+    ([160, 512, 200, 416], 512, 416),          # beside experts of two tiles, one of 160 rows
+    ([140, 210], 4096, 4096),                  # split along K
+])
+def test_bf16_one_row_tile_experts(counts, H, F):
+    _run(counts, H, F, None, len(counts), seed=sum(counts) + H)
+
+
 def test_bf16_resident_subset_and_slot_order():
     counts = [100, 200, 50, 300, 10, 0]
     slot = [2, -1, 0, -1, 1, 3]

@@ -73,3 +73,13 @@ def test_maps_only_many_chunks():
     r_off, r_rop, r_por, _ = oracle.permute(np.zeros((100_000, 1)), idx, 256)
     assert np.array_equal(to_host(off), r_off) and np.array_equal(to_host(rop), r_rop)
     assert np.array_equal(to_host(por), r_por)
+
+
+@pytest.mark.parametrize("T,E,k", [(1024, 8, 2), (1025, 8, 2), (683, 256, 3), (682, 256, 3),
+                                   (2048, 4, 1), (256, 256, 8), (8, 256, 256), (2, 7, 7)])
+def test_one_launch_limit(T, E, k):
+    # up to 2048 pairs every block counts all of them itself, beyond the counts
+    # come from a kernel of their own; both with a subset of the tokens
+    _run(T, E, k, 64, seed=T + E)
+    tok = np.sort(np.random.default_rng(T).permutation(T + 50)[:T]).astype(np.int32)
+    _run(T + 50, E, k, 32, seed=T, token_ids=tok, skew=1.2)
