@@ -119,6 +119,23 @@ def test_long_paths_read_from_memory():
     _check(routes, 256)
 
 
+@pytest.mark.parametrize("N,L,E,k", [
+    (1100, 128, 2, 2),      # rows of 256 bytes: staged, no room for padding
+    (1153, 4, 16, 2),       # padded rows of 8 bytes, one word, a last block of one token
+    (1100, 1, 64, 1), (1030, 3, 40, 1),   # one and two words: the later sort keys are zero
+    (1090, 65, 4, 4),       # rows of 260 bytes: not staged
+])
+def test_packing_shapes(N, L, E, k):
+    # beyond the one-block path, so paths are packed by their own kernel
+    routes = np.ascontiguousarray(synth.predicted_routes(N, L, E, k, 0.6, 1.0, seed=N + L),
+                                  dtype=np.uint8)
+    perm, demand, info = ops.schedule(to_dev(routes), E)
+    rp, rd, ri = oracle.schedule(routes, E)
+    assert to_host(info).tolist() == ri.tolist()
+    assert np.array_equal(to_host(perm), rp)
+    assert np.array_equal(to_host(demand), rd)
+
+
 # ----------------------------------------------------------------- B batches
 def _check_multi(routes, E, B, max_iters=10, keep=True):
     routes = np.ascontiguousarray(routes, dtype=np.uint8)
