@@ -161,3 +161,10 @@ def test_width_32_unaligned_weights():
     torch.cuda.synchronize()
     assert (l0 - l1).abs().max() <= 1e-4 * l0.abs().max() + 1e-5
     assert (p0 - p1).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("d,h,S", [(8, 1, 70), (16, 2, 33), (24, 3, 130), (64, 8, 65)])
+def test_heads_of_8_at_other_widths(d, h, S):
+    # attention on MFMAs beside the general kernels
+    _check(dict(PAPER, vocab=200, d_model=d, n_heads=h, d_ff=40, n_enc=1, n_dec=2, L=2, E=5), 2, S,
+           seed=90 + d)
