@@ -353,25 +353,27 @@ ffn_gemm_bf16(const uint16_t* __restrict__ A, int64_t K,
 // ------------------------------------------------------- few rows per expert
 // An expert with few rows (decode-sized batches) is bound by reading its
 // weights once, not by MFMA. A block owns one unit: COLS output columns
-// (weight rows) of one item of at most 96 rows; its waves split the K range
-// (contiguous parts, in 64-wide blocks), each streaming its part of those
-// weight rows through 16x16x32 MFMAs (the rows padded to 16 * MT), and the
-// partial sums are added through LDS in wave order.
+// (weight rows) of one item of at most 96 rows. The K range is cut into four
+// contiguous quarters of 32-wide steps; a wave streams one quarter of its weight
+// rows through 16x16x32 MFMAs in ascending K (the rows padded to 16 * MT), and
+// the four partial sums are added through LDS in quarter order: a result is the
+// same whichever shape of unit computes it.
 // Weights are loaded non-temporally, 8 rows x 128 bytes an instruction: whole
 // cache lines. Plain streaming of 1.9 GB this way runs at 6.9 TB/s, with 16
 // rows x 64 bytes, the layout the MFMA takes, at 5.2 (6.0 without the
 // non-temporal hint). Two such loads hold 16 rows x 64 k; lanes l and l ^ 8
 // swap one half of theirs (a row rotation by 8 under a bank mask, one
 // instruction a register), which leaves two MFMA operands: lane (row r, q)
-// holds the 16-byte chunk 2q of the row's line in the first and 2q + 1 in the
-// second, and the activation rows are read in the same order.
+// holds the 16-byte chunk q of the row's line in the first and 4 + q in the
+// second, the two K steps of the line. A quarter that begins or ends in the
+// middle of a line takes that half with one 16-row x 64-byte load.
 // Three shapes. kWide, 4 waves and four 16-column weight tiles a unit (32
 // columns of gate and of up, or 64 of down): fewest activation loads per weight
-// byte, two blocks per compute unit. kMid, the same unit with 8 waves, for
-// launches whose wide units are no more than the compute units. kNarrow, 8 waves
-// and one 16-column tile (of gate and of up, or of down), where those are no
-// more than the compute units either (one expert of width 5632 has 32 wide
-// units in its down projection, 128 narrow ones).
+// byte, two blocks per compute unit. kMid, the same unit with 8 waves, two of
+// the tiles each, for launches whose wide units are no more than the compute
+// units. kNarrow, one 16-column tile (of gate and of up with 8 waves, or of down
+// with 4), where those are no more than the compute units either (one expert of
+// width 5632 has 32 wide units in its down projection, 128 narrow ones).
 constexpr int kSmallRC = 2;                      // row tiles per LDS reduction pass
 
 constexpr int kWide = 0, kMid = 1, kNarrow = 2;
@@ -381,13 +383,14 @@ struct SmallShape {
   static constexpr int NB = EPI == 0 ? 2 : 1;    // gate and up, or down
   static constexpr int NT = SHAPE == kNarrow ? 1 : 4 / NB;   // 16-column MFMA tiles per unit
   static constexpr int COLS = 16 * NT;
-  static constexpr int WAVES = SHAPE == kWide ? 4 : 8;
+  static constexpr int WAVES = SHAPE == kWide || (SHAPE == kNarrow && EPI == 1) ? 4 : 8;
+  static constexpr int TPW = NT * NB * 4 / WAVES;            // weight tiles per wave
 };
 
-// K blocks of 64 loaded per batch: as many as the registers hold beside the
-// accumulators
-template <int MT, int SHAPE>
-constexpr int small_unroll() { return (MT <= 2 ? 2 : 1) * (SHAPE == kNarrow ? 2 : 1); }
+// K blocks of 64 loaded per batch: eight weight tiles of them a wave while the
+// rows are few, half of that beside the activations of more row tiles
+template <int MT, int TPW>
+constexpr int small_unroll() { return (MT == 1 || (MT == 2 && TPW > 1) ? 8 : MT <= 2 || TPW > 1 ? 4 : 2) / TPW; }
 
 __device__ __forceinline__ uint32_t ror8_into(uint32_t keep, uint32_t from, bool high) {
   // lanes 8..15 (high) or 0..7 of each row of 16 take `from` of the lane 8 away
@@ -401,16 +404,16 @@ __device__ __forceinline__ uint32_t ror8_into(uint32_t keep, uint32_t from, bool
 // by block 0 for the down projection), instead of coming from the tile-list
 // kernel: saves that launch where nothing needs the large tiles.
 template <int EPI, int MTMAX, int SHAPE>
-__global__ void __launch_bounds__(SHAPE == kWide ? 256 : 512) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__((64 * SmallShape<EPI, SHAPE>::WAVES)) __attribute__((amdgpu_waves_per_eu(2)))
 ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __restrict__ B0,
                const uint16_t* __restrict__ B1, int64_t F, int64_t H,
                const int32_t* __restrict__ offsets, const int32_t* __restrict__ slot, int E, int S,
                int64_t max_rows, int build, int32_t* __restrict__ small,
                uint16_t* __restrict__ C) {
   using SS = SmallShape<EPI, SHAPE>;
-  constexpr int NB = SS::NB, NT = SS::NT, W = SS::WAVES;
+  constexpr int NB = SS::NB, NT = SS::NT, W = SS::WAVES, TPW = SS::TPW;
   constexpr int RC = MTMAX < kSmallRC ? MTMAX : kSmallRC;
-  __shared__ f32x4_t part[W][RC][NT][NB][kWave];
+  __shared__ f32x4_t part[4][RC][NT * NB][kWave];
   __shared__ int32_t s_list[EPI == 0 ? kMaxItems : 1];
   int n_items;
   const int32_t* list = small + 1;
@@ -441,20 +444,22 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int r = lane & 15;                       // A row / B column of this lane
   const int q4 = lane >> 4;                      // its slice of a K step
-  const int64_t k64 = K / 64;
-  const int64_t per = (k64 + W - 1) / W;
-  const int64_t kb = min(k64, wave * per), ke = min(k64, kb + per);
-  const bool odd32 = (K & 32) != 0 && wave == W - 1;   // K's last 32
+  const int quarter = wave & 3, t0 = (wave >> 2) * TPW;   // its K range and first weight tile
+  const int64_t ks = K / 32;
+  const int64_t per = (ks + 3) / 4;
+  const int64_t kb = min(ks, quarter * per), ke = min(ks, kb + per);
+  // whole lines are blocks b0 .. b1 - 1; a half line before and one after them
+  const bool head = (kb & 1) != 0 && kb < ke, tail = (ke & 1) != 0 && kb < ke;
+  const int64_t b0 = (kb + 1) / 2, b1 = max(b0, ke / 2);
   // byte offsets from a weight tile's first row: this lane's slice of an
   // 8-row x 128-byte load, and of a 16-row x 64-byte one
-  const uint32_t b_off = (uint32_t)(((int64_t)(lane & 7) * K + (lane >> 3) * 8) * 2);
+  const uint32_t b_off = (uint32_t)(((int64_t)(lane & 7) * K + (q4 + ((lane >> 3) & 1) * 4) * 8) * 2);
   const uint32_t b_off32 = (uint32_t)(((int64_t)r * K + q4 * 8) * 2);
   const uint32_t b_half = (uint32_t)(8 * K * 2);       // the tile's rows 8 to 15
   auto run_unit = [&](auto mt_c, int e, int cb, int m, int64_t lo) {
     constexpr int MT = decltype(mt_c)::value;
-    constexpr int U = small_unroll<MT, SHAPE>();
+    constexpr int U = small_unroll<MT, TPW>();
     const int s = slot ? slot[e] : e;
-    const int64_t kfull = kb + (ke - kb) / U * U;
     const int64_t n0 = (int64_t)cb * SS::COLS;
     // wave-uniform bases plus 32-bit lane offsets. With one row tile, lanes of
     // rows past m load nothing (masked off, so no data comes back) and feed
@@ -467,26 +472,23 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       a_on[i] = 16 * i + r < m;
-      a_off[i] = (uint32_t)((int64_t)min(16 * i + r, m - 1) * K * 2);
+      a_off[i] = (uint32_t)(((int64_t)min(16 * i + r, m - 1) * K + q4 * 8) * 2);
     }
     // a column tile past N_out (the last unit of a down projection whose
     // width is an odd multiple of 32) re-reads the unit's first tile and is
     // not stored
-    const char* b_base[NT][NB];
+    const char* b_base[TPW];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
+    for (int g = 0; g < TPW; ++g) {
+      const int j = (t0 + g) / NB;
       const int64_t n = n0 + 16 * j < N_out ? n0 + 16 * j : n0;
-      b_base[j][0] = reinterpret_cast<const char*>(B0 + ((int64_t)s * N_out + n) * K);
-      if constexpr (EPI == 0)
-        b_base[j][1] = reinterpret_cast<const char*>(B1 + ((int64_t)s * N_out + n) * K);
+      b_base[g] = reinterpret_cast<const char*>(((t0 + g) % NB == 0 ? B0 : B1) + ((int64_t)s * N_out + n) * K);
     }
-    f32x4_t acc[MT][NT][NB];
+    f32x4_t acc[MT][TPW];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[i][j][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int g = 0; g < TPW; ++g) acc[i][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     auto load_w = [&](const char* p) {
       return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
     };
@@ -498,57 +500,74 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
       c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                   __builtin_bit_cast(bf16x8_t, w), c, 0, 0, 0);
     };
-    auto blocks = [&](int64_t s0, auto n_c) {
-      constexpr int NS = decltype(n_c)::value;
-      u32x4_t a[NS][2][MT], w[NS][NT][NB][2];
+    struct Block { u32x4_t a[2][MT], w[TPW][2]; };
+    struct Half { u32x4_t a[MT], w[TPW]; };
+    auto load_block = [&](Block& k, int64_t blk) {
+      const int64_t kbyte = blk * 128;
 #pragma unroll
-      for (int u = 0; u < NS; ++u) {
-        const int64_t kbyte = (s0 + u) * 128;
+      for (int g = 0; g < TPW; ++g)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int hh = 0; hh < 2; ++hh) k.w[g][hh] = load_w(b_base[g] + kbyte + (b_off + hh * b_half));
 #pragma unroll
-          for (int b = 0; b < NB; ++b)
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-              w[u][j][b][hh] = load_w(b_base[j][b] + kbyte + (b_off + hh * b_half));
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-          for (int hh = 0; hh < 2; ++hh) a[u][hh][i] = load_a(i, kbyte + q4 * 32 + hh * 16);
-      }
-#pragma unroll
-      for (int u = 0; u < NS; ++u)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            u32x4_t w0, w1;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              w0[v] = ror8_into(w[u][j][b][0][v], w[u][j][b][1][v], true);
-              w1[v] = ror8_into(w[u][j][b][1][v], w[u][j][b][0][v], false);
-            }
-#pragma unroll
-            for (int i = 0; i < MT; ++i) {
-              mfma(acc[i][j][b], a[u][0][i], w0);
-              mfma(acc[i][j][b], a[u][1][i], w1);
-            }
-          }
+        for (int hh = 0; hh < 2; ++hh) k.a[hh][i] = load_a(i, kbyte + hh * 64);
     };
-    for (int64_t s0 = kb; s0 < kfull; s0 += U) blocks(s0, std::integral_constant<int, U>{});
-    for (int64_t s0 = kfull; s0 < ke; ++s0) blocks(s0, std::integral_constant<int, 1>{});
-    if (odd32) {
-      const int64_t kbyte = k64 * 128;
+    auto use_block = [&](const Block& k) {
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
+      for (int g = 0; g < TPW; ++g) {
+        u32x4_t w0, w1;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const u32x4_t w = load_w(b_base[j][b] + kbyte + b_off32);
-#pragma unroll
-          for (int i = 0; i < MT; ++i) mfma(acc[i][j][b], load_a(i, kbyte + q4 * 16), w);
+        for (int v = 0; v < 4; ++v) {
+          w0[v] = ror8_into(k.w[g][0][v], k.w[g][1][v], true);
+          w1[v] = ror8_into(k.w[g][1][v], k.w[g][0][v], false);
         }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) mfma(acc[i][g], k.a[0][i], w0);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) mfma(acc[i][g], k.a[1][i], w1);
+      }
+    };
+    auto load_half = [&](Half& k, int64_t step) {
+#pragma unroll
+      for (int g = 0; g < TPW; ++g) k.w[g] = load_w(b_base[g] + step * 64 + b_off32);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) k.a[i] = load_a(i, step * 64);
+    };
+    auto use_half = [&](const Half& k) {
+#pragma unroll
+      for (int g = 0; g < TPW; ++g)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) mfma(acc[i][g], k.a[i], k.w[g]);
+    };
+    // the blocks that do not fill a batch go with the half line: after the one
+    // before them, else ahead of the one after them (all conditions are uniform)
+    const int rem = (int)((b1 - b0) % U);
+    auto part_batch = [&](bool before, int64_t first, int n, bool after) {
+      Half h;
+      Block k[U > 1 ? U - 1 : 1];
+      if (before) load_half(h, kb);
+#pragma unroll
+      for (int u = 0; u < U - 1; ++u)
+        if (u < n) load_block(k[u], first + u);
+      if (after) load_half(h, ke - 1);
+      if (before) use_half(h);
+#pragma unroll
+      for (int u = 0; u < U - 1; ++u)
+        if (u < n) use_block(k[u]);
+      if (after) use_half(h);
+    };
+    if (head) part_batch(true, b0, rem, false);
+    const int64_t m0 = head ? b0 + rem : b0, m1 = head ? b1 : b1 - rem;
+    for (int64_t blk = m0; blk < m1; blk += U) {
+      Block k[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) load_block(k[u], blk + u);
+#pragma unroll
+      for (int u = 0; u < U; ++u) use_block(k[u]);
     }
-    // the waves' partial sums, RC row tiles at a time: every wave writes its
+    if (m1 < b1 || tail) part_batch(false, m1, (int)(b1 - m1), tail);
+    // the quarters' partial sums, RC row tiles at a time: every wave writes its
     // own, then wave q adds up the (row tile, column tile) groups g with
     // g % W == q and stores them. C layout of the 16x16 MFMA: lane holds
     // column (lane % 16), rows 4 * (lane / 16) + q of its 16-row tile.
@@ -558,9 +577,7 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
       for (int ii = 0; ii < RC; ++ii)
         if (i0 + ii < MT)
 #pragma unroll
-          for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) part[wave][ii][j][b][lane] = acc[i0 + ii][j][b];
+          for (int g = 0; g < TPW; ++g) part[quarter][ii][t0 + g][lane] = acc[i0 + ii][g];
       __syncthreads();
       const int groups = (MT - i0 < RC ? MT - i0 : RC) * NT;
       for (int g = wave; g < groups; g += W) {
@@ -569,9 +586,9 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
         f32x4_t t[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-          t[b] = part[0][ii][j][b][lane];
+          t[b] = part[0][ii][j * NB + b][lane];
 #pragma unroll
-          for (int q = 1; q < W; ++q) t[b] += part[q][ii][j][b][lane];
+          for (int q = 1; q < 4; ++q) t[b] += part[q][ii][j * NB + b][lane];
         }
         if (col >= N_out) continue;
 #pragma unroll

@@ -272,3 +272,73 @@ def test_bf16_many_experts_large_tiles():
     slot[res] = np.arange(len(res), dtype=np.int32)
     assert counts.sum() > 32 * E
     _run(counts, 64, 96, slot, len(res), seed=91)
+
+
+def _quarter_sum(a):
+    """a [..., K] summed as the few-row kernel sums it: four contiguous quarters
+    of 32-wide steps, each a float32 chain of whole steps in ascending K, added
+    in order."""
+    ks = a.shape[-1] // 32
+    steps = a.reshape(a.shape[:-1] + (ks, 32)).astype(np.float64).sum(-1)
+    per, total = -(-ks // 4), None
+    for q in range(4):
+        s = np.zeros(a.shape[:-1], np.float32)
+        for i in range(q * per, min(ks, (q + 1) * per)):
+            s = (s + steps[..., i]).astype(np.float32)
+        total = s if total is None else (total + s).astype(np.float32)
+    return total
+
+
+def _order_rows(K, n):
+    """n rows [n, K] whose sum depends on the order it is taken in: 2^26 at one
+    step, 3 at each of the next two (lost beside it, 8 without it), -2^26 in the
+    last quarter; for every step of the first two quarters and a bit beyond, then
+    such a pair within one step beside a 3 at another chunk of it."""
+    ks = K // 32
+    rows = np.zeros((n, K), np.float32)
+    last = 32 * (3 * -(-ks // 4))
+    for i in range(n):
+        s = i // 2 % max(1, min(ks // 2 + 2, last // 32 - 3))
+        if i % 2 == 0:
+            rows[i, 32 * s] = 2.0 ** 26
+            rows[i, 32 * (s + 1) + 9] = rows[i, 32 * (s + 2) + 23] = 3
+            rows[i, last] = -2.0 ** 26
+        else:
+            rows[i, 32 * s] = 2.0 ** 26
+            rows[i, 32 * s + 8] = 3
+            rows[i, 32 * (s + 1)] = -2.0 ** 26
+    return rows
+
+
+@pytest.mark.parametrize("K", [1408, 1024, 2080, 480])    # quarters of 11, 8, 17 and 4 steps
+@pytest.mark.parametrize("counts,N", [
+    ([3], 128), ([40], 128),                              # 16-column units
+    ([1] * 39 + [18], 128),                               # wide units of eight waves
+    ([1, 17, 33, 49, 65, 81] + [1] * 134, 128),           # wide units of four waves
+])
+def test_bf16_few_row_sum_order(counts, N, K):
+    # the sum's order is the same whichever units compute it, exactly: up
+    # projection (x of ones), then down projection (activations of ones)
+    E, rows = len(counts), _order_rows(K, N)
+    want = _quarter_sum(rows)
+    assert (want == 0).any() and (want != 0).any()
+    offsets = to_dev(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32))
+    R = sum(counts)
+    slot = to_dev(np.zeros(E, np.int32))                  # every expert: the same weights
+    bf = lambda a: to_dev(synth.bf16_bits(np.asarray(a, np.float32)))[None]
+    one = np.zeros((N, K), np.float32)
+    one[:, 0] = 1
+    pick = np.zeros((K, N), np.float32)
+    pick[np.arange(N), np.arange(N)] = 1
+    y = vals(ops.expert_ffn(bf(np.ones((R, K)))[0], offsets, bf(rows), bf(one), bf(pick),
+                            slot_of_expert=slot))
+    act = np.where(want > 80, want, want / (1 + np.exp(-np.minimum(want, 80))))
+    ref = synth.values(synth.bf16_bits(act.astype(np.float32)))
+    np.testing.assert_allclose(y[:, :N], np.broadcast_to(ref, (R, N)), rtol=2.0 ** -7, atol=0)
+    gate, up, x = np.zeros((K, N)), np.zeros((K, N)), np.zeros((R, N))
+    gate[:, 0] = 64                                       # silu(64) / 64 = 1
+    up[:, 0] = 2.0 ** -6
+    x[:, 0] = 1
+    y = vals(ops.expert_ffn(bf(x)[0], offsets, bf(gate), bf(up), bf(rows), slot_of_expert=slot))
+    ref = synth.values(synth.bf16_bits(want))
+    np.testing.assert_array_equal(y, np.broadcast_to(ref, (R, N)))
