@@ -350,6 +350,20 @@ ffn_gemm_bf16(const uint16_t* __restrict__ A, int64_t K,
   }
 }
 
+// Raw buffer over `elems` 16-bit values at p.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const uint16_t* p, int64_t elems) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, (int)(uint32_t)(elems * 2),
+                                           0x00027000);
+}
+
+// 16 bytes per lane of a raw buffer, from byte offset voff (lane) + soff (wave);
+// past its end: zeros. NT: non-temporal.
+template <bool NT>
+__device__ __forceinline__ u32x4_t buf_load16(rsrc_t rs, uint32_t voff, uint32_t soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, NT ? 2 : 0);
+}
+
 // ------------------------------------------------------- few rows per expert
 // An expert with few rows (decode-sized batches) is bound by reading its
 // weights once, not by MFMA. A block owns one unit: COLS output columns
@@ -370,10 +384,13 @@ ffn_gemm_bf16(const uint16_t* __restrict__ A, int64_t K,
 // Three shapes. kWide, 4 waves and four 16-column weight tiles a unit (32
 // columns of gate and of up, or 64 of down): fewest activation loads per weight
 // byte, two blocks per compute unit. kMid, the same unit with 8 waves, two of
-// the tiles each, for launches whose wide units are no more than the compute
-// units. kNarrow, one 16-column tile (of gate and of up with 8 waves, or of down
-// with 4), where those are no more than the compute units either (one expert of
-// width 5632 has 32 wide units in its down projection, 128 narrow ones).
+// the tiles each, for launches of at most two row tiles whose wide units are no
+// more than the compute units; with more rows the activations, which both halves
+// of its waves load, cost more than the waves give (one expert of 53 rows, H
+// 2048, F 5632: 49 us, 44 with kWide). kNarrow, 4 waves and one 16-column tile
+// (of gate and of up, or of down), where those are no more than the compute
+// units either (one expert of width 5632 has 32 wide units in its down
+// projection, 128 narrow ones).
 constexpr int kSmallRC = 2;                      // row tiles per LDS reduction pass
 
 constexpr int kWide = 0, kMid = 1, kNarrow = 2;
@@ -383,14 +400,17 @@ struct SmallShape {
   static constexpr int NB = EPI == 0 ? 2 : 1;    // gate and up, or down
   static constexpr int NT = SHAPE == kNarrow ? 1 : 4 / NB;   // 16-column MFMA tiles per unit
   static constexpr int COLS = 16 * NT;
-  static constexpr int WAVES = SHAPE == kWide || (SHAPE == kNarrow && EPI == 1) ? 4 : 8;
+  static constexpr int WAVES = SHAPE == kMid ? 8 : 4;
   static constexpr int TPW = NT * NB * 4 / WAVES;            // weight tiles per wave
 };
 
 // K blocks of 64 loaded per batch: eight weight tiles of them a wave while the
-// rows are few, half of that beside the activations of more row tiles
+// rows are few, half of that beside the activations of more row tiles (which
+// weigh most in a wave of one weight tile); no instance spills a register
 template <int MT, int TPW>
-constexpr int small_unroll() { return (MT == 1 || (MT == 2 && TPW > 1) ? 8 : MT <= 2 || TPW > 1 ? 4 : 2) / TPW; }
+constexpr int small_unroll() {
+  return (MT == 1 || (MT == 2 && TPW > 1) ? 8 : MT == 2 || TPW > 1 ? 4 : 2) / TPW;
+}
 
 __device__ __forceinline__ uint32_t ror8_into(uint32_t keep, uint32_t from, bool high) {
   // lanes 8..15 (high) or 0..7 of each row of 16 take `from` of the lane 8 away
@@ -459,59 +479,57 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
   auto run_unit = [&](auto mt_c, int e, int cb, int m, int64_t lo) {
     constexpr int MT = decltype(mt_c)::value;
     constexpr int U = small_unroll<MT, TPW>();
-    const int s = slot ? slot[e] : e;
+    const int s = __builtin_amdgcn_readfirstlane(slot ? slot[e] : e);
     const int64_t n0 = (int64_t)cb * SS::COLS;
-    // wave-uniform bases plus 32-bit lane offsets. With one row tile, lanes of
-    // rows past m load nothing (masked off, so no data comes back) and feed
-    // zeros; with more, every lane loads (rows past m read the item's last
-    // row, whose products land in rows that are never stored): most of those
-    // lanes are live, and the masks would cost registers.
-    const char* const a_base = reinterpret_cast<const char*>(A + lo * K);
+    // Raw buffers: 32-bit lane offsets, and the K position as the scalar offset,
+    // where pointers would take two registers and a vector addition each (66
+    // registers of the shapes of five and six row tiles were spilled). Rows past
+    // m lie past the end of the buffer: nothing is read and zeros are used.
+    const auto rs_a = make_rsrc(A + lo * K, m * K);
     uint32_t a_off[MT];
-    bool a_on[MT];
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      a_on[i] = 16 * i + r < m;
-      a_off[i] = (uint32_t)(((int64_t)min(16 * i + r, m - 1) * K + q4 * 8) * 2);
-    }
+    for (int i = 0; i < MT; ++i) a_off[i] = (uint32_t)(((int64_t)(16 * i + r) * K + q4 * 8) * 2);
     // a column tile past N_out (the last unit of a down projection whose
     // width is an odd multiple of 32) re-reads the unit's first tile and is
     // not stored
-    const char* b_base[TPW];
+    rsrc_t rs_b[TPW];
 #pragma unroll
     for (int g = 0; g < TPW; ++g) {
       const int j = (t0 + g) / NB;
       const int64_t n = n0 + 16 * j < N_out ? n0 + 16 * j : n0;
-      b_base[g] = reinterpret_cast<const char*>(((t0 + g) % NB == 0 ? B0 : B1) + ((int64_t)s * N_out + n) * K);
+      rs_b[g] = make_rsrc(((t0 + g) % NB == 0 ? B0 : B1) + ((int64_t)s * N_out + n) * K, 16 * K);
     }
     f32x4_t acc[MT][TPW];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int g = 0; g < TPW; ++g) acc[i][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    auto load_w = [&](const char* p) {
-      return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-    };
-    auto load_a = [&](int i, int64_t kbyte) {
-      return (MT > 1 || a_on[i]) ? *reinterpret_cast<const u32x4_t*>(a_base + kbyte + a_off[i])
-                                 : u32x4_t{0, 0, 0, 0};
-    };
     auto mfma = [&](f32x4_t& c, const u32x4_t& a, const u32x4_t& w) {
       c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                   __builtin_bit_cast(bf16x8_t, w), c, 0, 0, 0);
     };
+    // From three row tiles on, a batch's loads go out before its products, the
+    // activations first (they come from L2): left to the scheduler they sink
+    // between the products and few are in flight (60 experts of 64 rows, H 2048,
+    // F 1408: 330 us, in this order 289). With fewer rows it does better alone
+    // (16 rows: 197 us, 206 so ordered).
+    constexpr bool kMany = MT > 2;
     struct Block { u32x4_t a[2][MT], w[TPW][2]; };
     struct Half { u32x4_t a[MT], w[TPW]; };
     auto load_block = [&](Block& k, int64_t blk) {
-      const int64_t kbyte = blk * 128;
+      const uint32_t kbyte = (uint32_t)blk * 128;
+      auto acts = [&]() {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh) k.a[hh][i] = buf_load16<false>(rs_a, a_off[i] + hh * 64, kbyte);
+      };
+      if (kMany) acts();
 #pragma unroll
       for (int g = 0; g < TPW; ++g)
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) k.w[g][hh] = load_w(b_base[g] + kbyte + (b_off + hh * b_half));
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) k.a[hh][i] = load_a(i, kbyte + hh * 64);
+        for (int hh = 0; hh < 2; ++hh) k.w[g][hh] = buf_load16<true>(rs_b[g], b_off, kbyte + hh * b_half);
+      if (!kMany) acts();
     };
     auto use_block = [&](const Block& k) {
 #pragma unroll
@@ -530,9 +548,9 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
     };
     auto load_half = [&](Half& k, int64_t step) {
 #pragma unroll
-      for (int g = 0; g < TPW; ++g) k.w[g] = load_w(b_base[g] + step * 64 + b_off32);
+      for (int g = 0; g < TPW; ++g) k.w[g] = buf_load16<true>(rs_b[g], b_off32, (uint32_t)step * 64);
 #pragma unroll
-      for (int i = 0; i < MT; ++i) k.a[i] = load_a(i, step * 64);
+      for (int i = 0; i < MT; ++i) k.a[i] = buf_load16<false>(rs_a, a_off[i], (uint32_t)step * 64);
     };
     auto use_half = [&](const Half& k) {
 #pragma unroll
@@ -551,6 +569,7 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
       for (int u = 0; u < U - 1; ++u)
         if (u < n) load_block(k[u], first + u);
       if (after) load_half(h, ke - 1);
+      if (kMany) __builtin_amdgcn_sched_barrier(0);
       if (before) use_half(h);
 #pragma unroll
       for (int u = 0; u < U - 1; ++u)
@@ -563,6 +582,7 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
       Block k[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) load_block(k[u], blk + u);
+      if (kMany) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < U; ++u) use_block(k[u]);
     }
@@ -570,30 +590,34 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
     // the quarters' partial sums, RC row tiles at a time: every wave writes its
     // own, then wave q adds up the (row tile, column tile) groups g with
     // g % W == q and stores them. C layout of the 16x16 MFMA: lane holds
-    // column (lane % 16), rows 4 * (lane / 16) + q of its 16-row tile.
+    // column (lane % 16), rows 4 * (lane / 16) + q of its 16-row tile. The lane
+    // number is made opaque so that addresses are formed here, not kept in
+    // registers over the K loop.
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
 #pragma unroll
     for (int i0 = 0; i0 < MT; i0 += RC) {
 #pragma unroll
       for (int ii = 0; ii < RC; ++ii)
         if (i0 + ii < MT)
 #pragma unroll
-          for (int g = 0; g < TPW; ++g) part[quarter][ii][t0 + g][lane] = acc[i0 + ii][g];
+          for (int g = 0; g < TPW; ++g) part[quarter][ii][t0 + g][ln] = acc[i0 + ii][g];
       __syncthreads();
       const int groups = (MT - i0 < RC ? MT - i0 : RC) * NT;
       for (int g = wave; g < groups; g += W) {
         const int ii = g / NT, j = g % NT;
-        const int64_t col = n0 + 16 * j + r;
+        const int64_t col = n0 + 16 * j + (ln & 15);
         f32x4_t t[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-          t[b] = part[0][ii][j * NB + b][lane];
+          t[b] = part[0][ii][j * NB + b][ln];
 #pragma unroll
-          for (int q = 1; q < 4; ++q) t[b] += part[q][ii][j * NB + b][lane];
+          for (int q = 1; q < 4; ++q) t[b] += part[q][ii][j * NB + b][ln];
         }
         if (col >= N_out) continue;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int rr = 16 * (i0 + ii) + (lane >> 4) * 4 + q;
+          const int rr = 16 * (i0 + ii) + (ln >> 4) * 4 + q;
           if (rr >= m) continue;
           const float v = EPI == 0 ? swiglu(t[0][q], t[NB - 1][q]) : t[0][q];
           C[(lo + rr) * N_out + col] = f32_to_bf16(v);
@@ -605,14 +629,16 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
   // units (item, column block) in list order, the grid striding over them:
   // at any time the blocks work on neighbouring columns
   for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
-    const int32_t it = list[(int)(unit / ncb)];
+    // the same for the whole block, and known to be (scalar registers)
+    const int32_t it = __builtin_amdgcn_readfirstlane(list[(int)(unit / ncb)]);
     const int e = it & 255;
-    const int cb = (int)(unit % ncb);
+    const int cb = __builtin_amdgcn_readfirstlane((int)(unit % ncb));
     int64_t lo;
     const int64_t rows = expert_rows(offsets, slot, e, S, max_rows, &lo);
     const int64_t skip = (int64_t)(it >> 8) * kSmallRows;
-    lo += skip;
-    const int m = (int)min(rows - skip, (int64_t)kSmallRows);   // 1 .. 16 * MTMAX (the list's rule)
+    lo = __builtin_amdgcn_readfirstlane((int)lo) + skip;        // rows are counted in 32 bits
+    // 1 .. 16 * MTMAX (the list's rule)
+    const int m = __builtin_amdgcn_readfirstlane((int)min(rows - skip, (int64_t)kSmallRows));
     const int mt = (m + 15) / 16;
     if (mt <= 1) run_unit(std::integral_constant<int, 1>{}, e, cb, m, lo);
     else if (mt == 2) { if constexpr (MTMAX >= 2) run_unit(std::integral_constant<int, 2>{}, e, cb, m, lo); }
@@ -630,13 +656,7 @@ __device__ __forceinline__ void lds_dma16(const void* g, void* lds_wave_base) {
   __builtin_amdgcn_global_load_lds(g, (lds_void*)lds_wave_base, 16, 0, 0);
 }
 
-// Raw buffer over `elems` 16-bit values at p, and a 16-byte-per-lane load of it
-// into LDS at byte offset voff (lane) + soff (wave).
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const uint16_t* p, int64_t elems) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, (int)(uint32_t)(elems * 2),
-                                           0x00027000);
-}
+// 16 bytes per lane of a raw buffer into LDS, from byte offset voff (lane) + soff (wave).
 __device__ __forceinline__ void buf_dma16(rsrc_t rs, uint32_t voff, uint32_t soff, void* lds_wave_base) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)lds_wave_base, 16, (int)voff, (int)soff, 0, 0);
 }
@@ -1521,6 +1541,12 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
           a, K, b0, b1, F, H, expert_offsets, slot_of_expert, E, S, max_rows, only_few ? 1 : 0,
           small, c);
     };
+    auto launch_mid = [&](auto epi_c, const uint16_t* a, int64_t K, const uint16_t* b0,
+                          const uint16_t* b1, uint16_t* c) {
+      const std::integral_constant<int, kMid> mid{};
+      if (mtmax == 1) launch_mt(epi_c, mid, std::integral_constant<int, 1>{}, a, K, b0, b1, c);
+      else launch_mt(epi_c, mid, std::integral_constant<int, 2>{}, a, K, b0, b1, c);
+    };
     auto launch_shape = [&](auto epi_c, auto shape_c, const uint16_t* a, int64_t K,
                             const uint16_t* b0, const uint16_t* b1, uint16_t* c) {
       if (mtmax == 1) launch_mt(epi_c, shape_c, std::integral_constant<int, 1>{}, a, K, b0, b1, c);
@@ -1534,8 +1560,8 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
       const int64_t n_out = EPI == 0 ? F : H;
       if (items * ceil_div(n_out, SmallShape<EPI, kNarrow>::COLS) <= cus)
         launch_shape(epi_c, std::integral_constant<int, kNarrow>{}, a, K, b0, b1, c);
-      else if (items * ceil_div(n_out, SmallShape<EPI, kMid>::COLS) <= cus)
-        launch_shape(epi_c, std::integral_constant<int, kMid>{}, a, K, b0, b1, c);
+      else if (mtmax <= 2 && items * ceil_div(n_out, SmallShape<EPI, kMid>::COLS) <= cus)
+        launch_mid(epi_c, a, K, b0, b1, c);
       else
         launch_shape(epi_c, std::integral_constant<int, kWide>{}, a, K, b0, b1, c);
     };

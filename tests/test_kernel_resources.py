@@ -1,0 +1,35 @@
+"""CPU checks of what the compiler made of the kernels: the resource notes that
+it writes beside each kernel of the built library."""
+import os
+import struct
+
+import pytest
+
+from paper_2410_17954_amd.build import library_path
+
+
+def _kernels():
+    msgpack = pytest.importorskip("msgpack")
+    if not os.path.exists(library_path()):
+        from paper_2410_17954_amd import build
+        build.build(verbose=False)
+    with open(library_path(), "rb") as f:
+        data = f.read()
+    out, at = {}, data.find(b"AMDGPU\0\0")
+    while at >= 0:                    # ELF notes: sizes of name and text, type, name, text
+        name_size, size, kind = struct.unpack("<III", data[at - 12:at])
+        if name_size == 7 and kind == 32:
+            notes = msgpack.unpackb(data[at + 8:at + 8 + size], strict_map_key=False)
+            out.update({k[".name"]: k for k in notes["amdhsa.kernels"]})
+        at = data.find(b"AMDGPU\0\0", at + 8)
+    return out
+
+
+def test_few_row_experts_spill_nothing():
+    # a reload in their K loop waits on the counter of the weight stream, and any
+    # scratch at all makes a launch of microseconds longer
+    few = {n: k for n, k in _kernels().items() if "ffn_small_bf16" in n}
+    assert len(few) >= 12
+    spilled = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"])
+               for n, k in few.items() if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
+    assert not spilled
