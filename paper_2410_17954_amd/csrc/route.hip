@@ -769,8 +769,8 @@ route_f32_kernel(const float* __restrict__ x, const float* __restrict__ wg, int6
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int e = lane + kWave * c;
-    taken[c] = e >= E;
     v[c] = e < E ? z64[e] : 0.0;
+    taken[c] = e >= E || v[c] != v[c];           // a NaN is never chosen
     if (e < E) mz = fmaxf(mz, (float)v[c]);
   }
   for (int o = 32; o > 0; o >>= 1) mz = fmaxf(mz, __shfl_xor(mz, o, kWave));
@@ -779,7 +779,8 @@ route_f32_kernel(const float* __restrict__ x, const float* __restrict__ wg, int6
     if (lane + kWave * c < E) total += expf((float)v[c] - mz);
   total = wave_sum(total);
   // k rounds of arg-max (larger value, then lower id); lane j keeps round j's
-  // winner (rounds past 63 in further registers)
+  // winner (rounds past 63 in further registers). Fewer than k numbers among
+  // the logits: id -1, gate 0.
   int win[4] = {0, 0, 0, 0};
   float ev[4] = {0.f, 0.f, 0.f, 0.f};
   float sel = 0.f;
@@ -800,7 +801,7 @@ route_f32_kernel(const float* __restrict__ x, const float* __restrict__ wg, int6
         be = oe;
       }
     }
-    const float g = expf((float)bv - mz);
+    const float g = be >= 0 ? expf((float)bv - mz) : 0.f;
     sel += g;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {

@@ -189,3 +189,40 @@ def test_f32_router(T, H, E, k, bias_kind):
         # a float32 exponential of a float32 difference, summed over E
         assert np.max(np.abs(to_host(gate) - oracle.gate_weights(z, ref, renorm))) <= 1e-5
         assert np.max(np.abs(to_host(lg) - z)) <= 2.0 ** -23 * np.max(np.abs(z))
+
+
+@pytest.mark.parametrize("renorm", [True, False])
+def test_f32_router_nan_and_infinities(renorm):
+    # NaN logits are never chosen and hide no other expert (6 shares a lane with
+    # 70, 134 and 198), -inf ones only after all others; a token whose hidden
+    # state is NaN gets no expert
+    T, H, E, k = 6, 40, 200, 6
+    g = np.random.default_rng(77)
+    x = g.standard_normal((T, H)).astype(np.float32)
+    w = (g.standard_normal((E, H)) * 0.2).astype(np.float32)
+    w[[6, 64, 199]] = np.nan
+    bias = g.standard_normal(E).astype(np.float32)
+    bias[[70, 134, 0]] = 20, 21, 19
+    bias[9:60] = -np.inf
+    x[4, 3] = np.nan
+    with np.errstate(invalid="ignore"):
+        z = x.astype(np.float64) @ w.astype(np.float64).T + bias
+    idx, gate, _ = ops.route(to_dev(x), to_dev(w), k, bias=to_dev(bias), renormalize=renorm)
+    idx, gate = to_host(idx), to_host(gate)
+    key = np.where(np.isnan(z), -np.inf, z)
+    for t in range(T):
+        if t == 4:
+            assert (idx[t] == -1).all() and np.isnan(gate[t]).all()
+            continue
+        ref = np.argsort(-key[t], kind="stable")[:k]
+        assert np.array_equal(idx[t], ref)
+        if renorm:
+            e = np.exp(z[t, ref] - z[t, ref].max())
+            assert np.max(np.abs(gate[t] - e / e.sum())) <= 1e-5
+        else:
+            assert np.isnan(gate[t]).all()        # the softmax runs over a NaN
+    # fewer numbers than k
+    idx, gate, _ = ops.route(to_dev(x[:1]), to_dev(w[5:8]), 3, renormalize=True)
+    z = x[:1].astype(np.float64) @ w[[5, 7]].astype(np.float64).T
+    a, b = (5, 7) if z[0, 0] >= z[0, 1] else (7, 5)
+    assert to_host(idx)[0].tolist() == [a - 5, b - 5, -1] and to_host(gate)[0, 2] == 0
