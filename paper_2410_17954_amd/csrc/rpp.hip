@@ -329,12 +329,24 @@ rpp_attention8(const float* __restrict__ Q, int64_t ldq, const float* __restrict
     mx = nm;
     den *= scale;
     // the block's own sum first: chains of 64 products, then one per 64 keys
+    // (the causal diagonal: keys past the first query are masked for some of
+    // the queries, p = 0, and a value of theirs that is not finite stays out of
+    // the products)
+    const bool diagonal = causal && j0 + 63 > i0;
+    bool odd = false;
     f32x4_t blk = {0.f, 0.f, 0.f, 0.f};
     float dblk = 0.f;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const float4 vv = *reinterpret_cast<const float4*>(vt + (r & 7) * vp + j0 + 16 * t + 4 * q4);
-      const float va[4] = {vv.x, vv.y, vv.z, vv.w};
+      float va[4] = {vv.x, vv.y, vv.z, vv.w};
+      if (diagonal)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (j0 + 16 * t + 4 * q4 + v > i0 && !isfinite(va[v])) {
+            va[v] = 0.f;
+            odd = true;
+          }
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float p = __expf(sc[t][v] - nm);
@@ -343,6 +355,24 @@ rpp_attention8(const float* __restrict__ Q, int64_t ldq, const float* __restrict
       }
     }
     den += dblk;
+    if (ballot(odd)) {                               // for the queries that see them
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float p = __expf(sc[t][v] - nm);
+          for (int g = 0; g < 4; ++g) {
+            const int j = j0 + 16 * t + 4 * g + v;
+            const float pj = __shfl(p, r + 16 * g);
+            if (j <= i0 || j > i0 + r) continue;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const float val = vt[((4 * q4 + c) & 7) * vp + j];
+              if (!isfinite(val)) blk[c] = fmaf(pj, val, blk[c]);
+            }
+          }
+        }
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[v] = fmaf(acc[v], scale, blk[v]);
   }

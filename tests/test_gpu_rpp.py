@@ -168,3 +168,26 @@ def test_heads_of_8_at_other_widths(d, h, S):
     # attention on MFMAs beside the general kernels
     _check(dict(PAPER, vocab=200, d_model=d, n_heads=h, d_ff=40, n_enc=1, n_dec=2, L=2, E=5), 2, S,
            seed=90 + d)
+
+
+@pytest.mark.parametrize("at,S", [(20, 50), (40, 50), (63, 130), (64, 130), (71, 130)])
+def test_later_values_not_finite(at, S):
+    # a token whose value in the decoder's self-attention overflows float32:
+    # the positions before it do not see it and keep their results; those after do
+    dims = dict(PAPER, vocab=40, d_ff=64, n_enc=1, n_dec=1, L=3, E=7)
+    w = _weights(dims, 5).astype(np.float64)
+    p = orpp.unpack(w, dims)                  # views
+    p["emb"][:, 5] = 0
+    p["emb"][7, 5] = 10                       # about 4.7 after the norm, others 0
+    p["dec"][0]["v"][:, 5] = 3e38
+    w = w.astype(np.float32)
+    ids = np.random.default_rng(at).integers(8, 40, size=(2, S)).astype(np.int32)
+    ids[1, at] = 7
+    _, logits, _ = ops.rpp_forward(to_dev(ids), to_dev(w), dims, want_logits=True)
+    got = to_host(logits).astype(np.float64)
+    with np.errstate(all="ignore"):
+        _, ref = orpp.rpp_forward(ids, w.astype(np.float64), dims)
+    tol = 1e-4 * np.abs(ref[0]).max() + 1e-5
+    assert np.abs(got[0] - ref[0]).max() <= tol
+    assert np.abs(got[1, :at] - ref[1, :at]).max() <= tol
+    assert not np.isfinite(got[1, at:]).any()
