@@ -209,14 +209,14 @@ def test_bf16_few_rows_per_expert(counts, H, F):
 ])
 def test_bf16_few_rows_resident_subset(counts, slot, S, extra):
     # decode-sized batch (at most 64 rows per expert on average) with one
-    # expert large enough for the large tiles
+    # expert of more than one item, all of it for the few-row kernel
     _run(counts, 256, 384, slot, S, seed=23 + sum(counts), extra_rows=extra)
 
 
 def test_bf16_few_rows_many_experts_subset():
-    # decode-sized batch over 256 experts (the few-row list built from all of
-    # them, ids sorted by row tiles), a fifth of them not resident, many empty,
-    # one row past the few-row limit
+    # decode-sized batch over 256 experts (the list of items built from all of
+    # them, sorted by row tiles), a fifth of them not resident, many empty, one
+    # of two items
     g = np.random.default_rng(5)
     E = 256
     counts = np.where(g.random(E) < 0.4, 0, g.integers(1, 80, size=E))
@@ -226,6 +226,24 @@ def test_bf16_few_rows_many_experts_subset():
     slot[res] = np.arange(len(res), dtype=np.int32)
     assert counts.sum() <= 64 * E
     _run(counts, 64, 96, slot, len(res), seed=5, extra_rows=3)
+
+
+@pytest.mark.parametrize("counts,slot,H,F", [
+    ([130, 5, 60, 33], None, 2048, 2304),
+    ([130, 5, 60, 33], [1, -1, 2, 0], 2048, 2304),
+    ([5, 97, 0, 60], [-1, 0, 1, -1], 3072, 3072),         # the listed experts hold no rows or no slot
+    ([20, 260, 96, 1, 0, 33, 17], None, 1536, 1536),      # a last row tile of 4 rows
+    ([260, 20, 96, 1, 5, 33, 288], [0, 1, 2, -1, 3, 4, 5], 1536, 1536),   # of 4 and of 32 rows
+])
+def test_bf16_few_rows_beside_large_tiles(counts, slot, H, F):
+    # decode-sized batch whose weights are too large to be read once more per
+    # 96 rows: experts up to 96 rows are listed for the few-row kernel, the
+    # others take the large tiles of the same call
+    rows = sum(counts)
+    counts = counts + [0] * max(0, -(-rows // 64) - len(counts))
+    slot = None if slot is None else slot + [-1] * (len(counts) - len(slot))
+    assert 96 < rows <= 64 * len(counts) and (rows - 1) // 96 * 6 * H * F > 54e6
+    _run(counts, H, F, slot, len(counts) if slot is None else max(slot) + 1, seed=rows + H)
 
 
 def test_bf16_few_rows_nothing_to_do():

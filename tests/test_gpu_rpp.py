@@ -136,17 +136,19 @@ def test_other_widths(d, h):
     (2, 63, dict(d_ff=36)), (1, 64, dict(d_ff=4)), (1, 65, dict(d_ff=500)),   # key blocks; part of a chunk
     (33, 129, dict(d_ff=64)),                   # 4257 rows: 32 a block, the last one short
     (1, 910, dict(d_ff=64, n_enc=1, n_dec=1)),  # keys padded to 64 no longer fit LDS
-    (2, 40, dict(d_ff=50)), (2, 40, dict(num_buckets=34, max_distance=128, n_heads=1)),
+    (2, 40, dict(d_ff=50)), (2, 40, dict(num_buckets=4, n_heads=1)),
 ])
 def test_width_32_edges(B, S, over):
-    # float32 sums of at most 2048 terms, as the other cases; num_buckets 34 is
-    # refused (its halves are no powers of two), d_ff 50 takes the general kernels
-    dims = dict(PAPER, vocab=300, L=3, E=7, **over)
-    if dims["num_buckets"] == 34:
-        with pytest.raises(ops.MoeError):
-            _check(dims, B, S, seed=70)
-        return
-    _check(dims, B, S, seed=70 + S)
+    # float32 sums of at most 2048 terms, as the other cases; d_ff 50 takes the
+    # general kernels; the fewest buckets
+    _check(dict(PAPER, vocab=300, L=3, E=7, **over), B, S, seed=70 + S)
+
+
+@pytest.mark.parametrize("num_buckets", [2, 34, 24])
+def test_bucket_counts_refused(num_buckets):
+    # the buckets of each side have to split into halves of a power of two
+    with pytest.raises(ops.MoeError):
+        _check(dict(PAPER, vocab=300, L=3, E=7, num_buckets=num_buckets), 2, 40, seed=70)
 
 
 def test_width_32_unaligned_weights():

@@ -183,10 +183,12 @@ def test_multi_way_mixtral_unit_four_batches():
     assert ro.tolist() == [0, 2048, 4096, 6144, 8192]
 
 
-def test_multi_way_demand_too_large_for_lds():
-    # 70 layers x 256 experts: the per-batch demand counts go straight to memory
+@pytest.mark.parametrize("B", [3, 1])
+def test_multi_way_demand_too_large_for_lds(B):
+    # 70 layers x 256 experts, too many cells for LDS: with three batches the
+    # splits leave the demand, of a single one it is counted straight to memory
     routes = synth.predicted_routes(300, 70, 256, 2, 0.7, 1.0, seed=54)
-    _check_multi(routes, 256, 3)
+    _check_multi(routes, 256, B)
 
 
 def test_multi_way_many_small_nodes_per_level():
