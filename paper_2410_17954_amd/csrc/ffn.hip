@@ -53,8 +53,8 @@ constexpr int kCounterWords = kClaimWords + 2 * kTailWords;
 constexpr int kSmallMaxTiles = 6;
 constexpr int kSmallRows = 16 * kSmallMaxTiles;
 constexpr int kMaxExperts = 256;
-// chunks beyond each expert's first that a launch without the large tiles may hold
-constexpr int kMaxExtraItems = 176;
+// chunks beyond each expert's first: at most 64 rows per expert on average
+constexpr int kMaxExtraItems = (64 * kMaxExperts - 1) / kSmallRows;
 constexpr int kMaxItems = kMaxExperts + kMaxExtraItems;
 
 // Rows of expert e, 0 when it is not resident; *lo: its first row.
@@ -651,10 +651,6 @@ ffn_small_bf16(const uint16_t* __restrict__ A, int64_t K, const uint16_t* __rest
 
 // ------------------------------------------------------- LDS DMA helpers
 typedef __attribute__((address_space(3))) void lds_void;
-
-__device__ __forceinline__ void lds_dma16(const void* g, void* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds(g, (lds_void*)lds_wave_base, 16, 0, 0);
-}
 
 // 16 bytes per lane of a raw buffer into LDS, from byte offset voff (lane) + soff (wave).
 __device__ __forceinline__ void buf_dma16(rsrc_t rs, uint32_t voff, uint32_t soff, void* lds_wave_base) {
@@ -1495,7 +1491,7 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
   // costs reading its weights once more per item, some 9 us for 54 MB. At
   // that size and below the few-row kernel takes every expert.
   const int64_t extra = few ? (max_rows - 1) / kSmallRows : 0;
-  const bool only_few = few && extra <= kMaxExtraItems && extra * 6 * H * F <= 54 * 1000 * 1000;
+  const bool only_few = few && extra * 6 * H * F <= 54 * 1000 * 1000;
   const bool big = !only_few;
   if (big) {
     ffn_tiles_kernel<<<dim3(1), dim3(kMaxExperts), 0, st>>>(expert_offsets, slot_of_expert, E, S,

@@ -2148,25 +2148,22 @@ __global__ void sch_multi_zero(int64_t n, int32_t* __restrict__ p) {
   if (i < n) p[i] = 0;
 }
 
-// demand[b, l, e] = tokens of batch b whose route uses (l, e). Block (c, b)
-// counts kDemandChunk tokens of batch b into an LDS histogram when L*E fits
-// (else straight into memory), then adds it to demand (zeroed first): many
-// blocks per batch keep the LDS atomics on the few (l, e) cells of small E
-// from serialising. Only for a single batch: a split knows its halves' counts. A token repeating an expert within a layer counts once.
+// demand[l, e] = tokens whose route uses (l, e), for a single batch of all
+// tokens (a split knows its halves' counts). A block counts kDemandChunk tokens
+// into an LDS histogram when L*E fits (else straight into memory), then adds it
+// to demand (zeroed first): many blocks keep the LDS atomics on the few (l, e)
+// cells of small E from serialising. A token repeating an expert within a layer
+// counts once.
 constexpr int kDemandLdsWords = 16384;
 constexpr int kDemandChunk = 256;
 template <bool LDS>
 __global__ void __launch_bounds__(256)
-sch_multi_demand(const uint8_t* __restrict__ routes, const int32_t* __restrict__ perm,
-                 const int32_t* __restrict__ offsets, int32_t L, int32_t E, int32_t k,
+sch_multi_demand(const uint8_t* __restrict__ routes, int64_t N, int32_t L, int32_t E, int32_t k,
                  int32_t* __restrict__ demand) {
   __shared__ int32_t h[LDS ? kDemandLdsWords : 1];
-  const int b = blockIdx.y;
   const int64_t LE = (int64_t)L * E;
-  int32_t* const out = demand + (int64_t)b * LE;
-  const int64_t lo = offsets[b] + (int64_t)blockIdx.x * kDemandChunk;
-  const int64_t hi = min((int64_t)offsets[b + 1], lo + kDemandChunk);
-  if (lo >= hi) return;                                // uniform over the block
+  const int64_t lo = (int64_t)blockIdx.x * kDemandChunk;
+  const int64_t hi = min(N, lo + kDemandChunk);
   if (LDS) {
     for (int64_t q = threadIdx.x; q < LE; q += blockDim.x) h[q] = 0;
     __syncthreads();
@@ -2175,20 +2172,20 @@ sch_multi_demand(const uint8_t* __restrict__ routes, const int32_t* __restrict__
   for (int64_t q = threadIdx.x; q < total; q += blockDim.x) {
     const int64_t p = lo + q % (hi - lo);              // neighbouring threads: neighbouring tokens
     const int l = (int)(q / (hi - lo));
-    const uint8_t* r = routes + ((int64_t)perm[p] * L + l) * k;
+    const uint8_t* r = routes + (p * L + l) * k;
     for (int j = 0; j < k; ++j) {
       bool seen = false;
       for (int jj = 0; jj < j; ++jj) seen |= r[jj] == r[j];
       if (seen || r[j] >= E) continue;
       const int64_t cell = (int64_t)l * E + r[j];
       if (LDS) atomicAdd(&h[cell], 1);
-      else atomicAdd(&out[cell], 1);
+      else atomicAdd(&demand[cell], 1);
     }
   }
   if (LDS) {
     __syncthreads();
     for (int64_t q = threadIdx.x; q < LE; q += blockDim.x)
-      if (h[q]) atomicAdd(&out[q], h[q]);
+      if (h[q]) atomicAdd(&demand[q], h[q]);
   }
 }
 
@@ -2331,11 +2328,9 @@ extern "C" int moe_schedule_multi(const uint8_t* routes, int64_t N, int32_t L, i
     MOE_CHECK_LAUNCH();
     const dim3 g((unsigned)ceil_div(N, kDemandChunk));
     if (LE <= kDemandLdsWords)
-      sch_multi_demand<true><<<g, dim3(256), 0, st>>>(routes, perm, batch_offsets, L, E, k,
-                                                       demand);
+      sch_multi_demand<true><<<g, dim3(256), 0, st>>>(routes, N, L, E, k, demand);
     else
-      sch_multi_demand<false><<<g, dim3(256), 0, st>>>(routes, perm, batch_offsets, L, E, k,
-                                                        demand);
+      sch_multi_demand<false><<<g, dim3(256), 0, st>>>(routes, N, L, E, k, demand);
     MOE_CHECK_LAUNCH();
   }
   return MOE_OK;
