@@ -1446,11 +1446,11 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
   void* act = ws;
   int32_t* prefix = reinterpret_cast<int32_t*>(ws + align_up((size_t)max_rows * F * elt, 256));
 
+  const uintptr_t at = reinterpret_cast<uintptr_t>(x_perm) | reinterpret_cast<uintptr_t>(w_gate) |
+                       reinterpret_cast<uintptr_t>(w_up) | reinterpret_cast<uintptr_t>(w_down);
   if (dtype == MOE_F32) {
     // 16-byte loads, and a grid that covers every expert's row groups
     const int64_t groups = ceil_div(max_rows, kF32Rows) + std::min<int64_t>(E, max_rows);
-    const uintptr_t at = reinterpret_cast<uintptr_t>(x_perm) | reinterpret_cast<uintptr_t>(w_gate) |
-                         reinterpret_cast<uintptr_t>(w_up) | reinterpret_cast<uintptr_t>(w_down);
     if (H % 4 == 0 && F % 4 == 0 && (at & 15) == 0 && groups <= 65535) {
       ffn_f32_mfma<0><<<dim3((unsigned)ceil_div(F, 16), (unsigned)groups), dim3(64 * kF32Waves), 0, st>>>(
           static_cast<const float*>(x_perm), H, static_cast<const float*>(w_gate),
@@ -1476,7 +1476,8 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
     return MOE_OK;
   }
 
-  const bool fast = fast_path(H, F);
+  // buffer loads and DMA of 16 bytes; the general path's loads take any address
+  const bool fast = fast_path(H, F) && (at & 15) == 0;
   const int bm = fast ? fast::BM : BM;
   // Experts with at most 16 * kSmallMaxTiles rows go to the weight-streaming
   // kernel when the batch is decode-sized (at most 64 rows per expert on

@@ -360,3 +360,23 @@ def test_bf16_few_row_sum_order(counts, N, K):
     y = vals(ops.expert_ffn(bf(x)[0], offsets, bf(gate), bf(up), bf(rows), slot_of_expert=slot))
     ref = synth.values(synth.bf16_bits(want))
     np.testing.assert_array_equal(y, np.broadcast_to(ref, (R, N)))
+
+
+@pytest.mark.parametrize("counts", [[3, 40, 1], [300, 20, 513]])     # few rows; large tiles
+@pytest.mark.parametrize("which", ["x", "w_gate", "w_down"])
+def test_bf16_operands_off_16_bytes(which, counts):
+    # an operand that starts 8 bytes past a 16-byte boundary takes the general
+    # kernels; bound of the other bf16 cases
+    H, F, S = 128, 192, len(counts)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    x = _rows(offsets[-1], H, 3)
+    ws = dict(zip(("w_gate", "w_up", "w_down"), _weights(S, F, H, 3)))
+    dev = dict({n: to_dev(w) for n, w in ws.items()}, x=to_dev(x))
+    buf = torch.zeros(dev[which].numel() + 4, dtype=torch.bfloat16, device="cuda:0")
+    buf[4:] = dev[which].reshape(-1)
+    dev[which] = buf[4:].view(dev[which].shape)
+    assert dev[which].data_ptr() % 16 == 8
+    y = ops.expert_ffn(dev["x"], to_dev(offsets), dev["w_gate"], dev["w_up"], dev["w_down"])
+    ref, _ = oracle.expert_ffn(synth.values(x), offsets, np.arange(S),
+                               *(synth.values(ws[n]) for n in ("w_gate", "w_up", "w_down")))
+    assert rel_max_err(vals(y), ref) <= 1e-2
