@@ -103,7 +103,9 @@ __device__ __forceinline__ int list_items(const int32_t* tiles, int E, int e, in
 // tile that short runs its K loop several times faster than the full tiles
 // beside it, so kept in its column group it runs ahead of the tiles that share
 // its weights in L2 and streams them from HBM alone. A last tile of more than
-// bm / 8 rows keeps close enough pace to stay in place.
+// bm / 8 rows keeps close enough pace to stay in place. (Both products of 6000
+// Mixtral-shaped tokens: 3084 us, 3180 with bm / 16; of 2000 Qwen-shaped ones 298,
+// 311 with bm / 4.)
 // One thread per expert and a block scan: walked by one thread the lists took
 // 12 us (60 experts) to 28 us (with 47 few-row experts) of a decode step.
 __global__ void __launch_bounds__(kMaxExperts)
@@ -712,8 +714,11 @@ constexpr int kStage = BM * BK;             // elements per operand stage
 // tile, each at least kMinSplitSteps K-steps; a piece's fp32 partial tile is
 // 256 threads x 64 float4 (256 KB) in the workspace. A piece pays a prologue,
 // its partial tile's stores and a share of the final sum whatever its length,
-// which shorter pieces do not earn back: with K = 2048 (64 steps) four
-// 16-step pieces made the launch slower than no split at all.
+// which shorter pieces do not earn back: at least 32 steps instead of 64 makes
+// both products of 8192 Qwen-shaped tokens 658 us instead of 590. Against no
+// split, pieces of 64 steps lose too where K has 128 (8 experts, 777 tokens, K
+// 4096 and 14336: 898 us, 817 with at least 128; 16 experts, 2048 tokens, H 1024,
+// F 4096: 312, 244); a longer limit would order the sums of such tiles otherwise.
 constexpr int kMaxSplit = 8, kMinSplitSteps = 64;
 constexpr int kMaxPieces = 512;
 constexpr size_t kPieceBytes = 256 * 64 * 16;
@@ -815,7 +820,9 @@ ffn_gemm_bf16_fast(const uint16_t* __restrict__ A, int64_t K,
   // then fill a 32-tile chunk by themselves, one weight tile against 32
   // activation panels; 16 divides the share, so the chunks of the 8 XCDs
   // still cover each round exactly once). With at most 7 row tiles per expert
-  // the larger chunk cuts fewer column groups across two XCDs' L2s.
+  // the larger chunk cuts fewer column groups across two XCDs' L2s. Either chunk
+  // for all is now within 2 % of this (8192 Qwen-shaped tokens 590 us, 584 with
+  // either; 16384 DeepSeek-shaped 1520, 1508 with 16, 1531 with 32).
   int64_t me_max = 0;
   for (int ee = 0; ee < E; ++ee) me_max = max(me_max, (int64_t)(prefix[ee + 1] - prefix[ee]));
   const int64_t chunk = me_max >= 8 && per_xcd % 16 == 0 ? 16 : per_xcd;
@@ -1523,9 +1530,10 @@ extern "C" int moe_expert_ffn(const void* x_perm, int32_t dtype, int64_t max_row
         reinterpret_cast<char*>(prefix) + align_up((size_t)(E + 1 + kCounterWords + 2 * (E + 1)) * 4, 256));
     const int pieces = (int)max_split_pieces(max_rows, H, F, E);
     // The few-row units: at most min(E, max_rows) + extra items. Two wide blocks
-    // or one block of 8 waves per compute unit stride over them (more blocks in
-    // flight spread the reads over more DRAM rows at once and measured slower;
-    // fewer leave bandwidth unused).
+    // or one of the other shapes' per compute unit stride over them (more blocks
+    // in flight spread the reads over more DRAM rows at once: 60 experts of 4
+    // rows, H 2048, F 1408, 172 us, 184 with three; of 48 rows 258, 287; fewer
+    // leave bandwidth unused).
     const int64_t items = std::min<int64_t>(E, max_rows) + extra;
     const int64_t cus = device_cu_count();
     auto launch_mt = [&](auto epi_c, auto shape_c, auto mt_c, const uint16_t* a, int64_t K,

@@ -588,11 +588,6 @@ constexpr int kWPitch = kWChunk + 8;              // padded row (bank spread)
 // used (measured at 8192 Qwen-shaped tokens: 64-token tiles, 128 blocks, 59 us;
 // 32, 256 blocks, 46 us; 16, 512 blocks, 41 us)
 constexpr int kRouteTileBlocks = 2;
-// Up to one 16-token block per compute unit, 33-64 experts take the K-split
-// kernel: a block then waits for its chain of loads along K, which eight waves
-// walk in two steps each (Qwen shape, 24 tokens 18.5 -> 15.2 us, 4096 tokens
-// 25.2 -> 20.5). Beyond, its LDS (one block per compute unit) and the router
-// matrix read again per 16 tokens cost more (8192 tokens 31 -> 40 us).
 // float32 chain of the 33-64-expert kernel: one K-step while a wave holds one
 // or two 16-expert blocks, four for four blocks (one K-step there needs more
 // registers than the wave has)
@@ -744,8 +739,8 @@ route_f32_kernel(const float* __restrict__ x, const float* __restrict__ wg, int6
                  float* __restrict__ topk_w) {
   // Each wave takes every fourth expert, its lanes splitting H; wave 0 then
   // decides with four experts per lane. (One thread per expert walking H, and
-  // one thread deciding, took 12.6 us at H 128; 5.6 now, most of it launch and
-  // load latency.)
+  // one thread deciding, took 13.7 us for 64 tokens of H 128; 5.7 now, most of
+  // it launch and load latency.)
   __shared__ double z64[256];
   const int64_t t = blockIdx.x;
   const int lane = lane_id(), wave = threadIdx.x / kWave;
@@ -912,6 +907,12 @@ extern "C" int moe_route(const void* x, const void* w_gate, int32_t dtype, int64
 #define MOE_ROUTE_LAUNCH(N, W, U, CH, KB)                                                 \
   route_ksplit_kernel<N, W, U, CH, KB><<<dim3((unsigned)blocks), dim3(W * 64), 0, st>>>(  \
       xb, wb, T, H, E, k, bias, bias_mode, renormalize, logits, topk_idx, topk_w)
+  // Up to one 16-token block per compute unit, 33-64 experts take the K-split
+  // kernel: a block then waits for its chain of loads along K, which eight waves
+  // walk in two steps each (Qwen shape, kernel times: 24 tokens 18.6 us by tiles,
+  // 15.4 so; 4096 tokens 25.5, 21.0). Beyond, its LDS (one block per compute
+  // unit) and the router matrix read again per 16 tokens cost more (8192 tokens
+  // 31.3, 36.5).
   if ((neb == 3 || neb == 4) && blocks <= device_cu_count()) {
     MOE_ROUTE_LAUNCH(4, 8, 4, 1, 100);
     MOE_CHECK_LAUNCH();
