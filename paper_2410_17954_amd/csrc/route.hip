@@ -478,6 +478,12 @@ route_ksplit_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__
   for (int64_t s0 = s_beg; s0 < s_end; s0 += U > CH ? U : CH) {
     constexpr int R = U > CH ? U : CH;            // K-steps of a round
     static_assert(R % U == 0 && R % CH == 0, "whole chains and load batches");
+    // a chain over several load batches (tested for inside them, its moves between
+    // registers cost 65 experts 5 %)
+    if constexpr (U < CH) {
+#pragma unroll
+      for (int nb = 0; nb < NEB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
     const int64_t c_end = min(s_end, s0 + R);
     for (int64_t s1 = s0; s1 < c_end; s1 += U) {
       uint4 a[U];
@@ -500,23 +506,30 @@ route_ksplit_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__
       for (int u = 0; u < U; ++u) {
         const bf16x8_t av = __builtin_bit_cast(bf16x8_t, a[u]);
         const bf16x8_t aa = __builtin_bit_cast(bf16x8_t, abs_bf16x8(a[u]));
-        const bool first = U >= CH ? u % CH == 0 : (s1 == s0 && u == 0);
-        const bool last = U >= CH ? (u + 1) % CH == 0 : (s1 + U >= c_end && u == U - 1);
+        if constexpr (U >= CH)
+          if (u % CH == 0)
+#pragma unroll
+            for (int nb = 0; nb < NEB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int nb = 0; nb < NEB; ++nb) {
-          if (first) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
           acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               av, __builtin_bit_cast(bf16x8_t, b[u][nb]), acc[nb], 0, 0, 0);
           acs[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               aa, __builtin_bit_cast(bf16x8_t, abs_bf16x8(b[u][nb])), acs[nb], 0, 0, 0);
         }
-        if (last) {
+        if constexpr (U >= CH)
+          if ((u + 1) % CH == 0)
 #pragma unroll
-          for (int nb = 0; nb < NEB; ++nb)
+            for (int nb = 0; nb < NEB; ++nb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a64[nb][i] += (double)acc[nb][i];
-        }
+              for (int i = 0; i < 4; ++i) a64[nb][i] += (double)acc[nb][i];
       }
+    }
+    if constexpr (U < CH) {
+#pragma unroll
+      for (int nb = 0; nb < NEB; ++nb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a64[nb][i] += (double)acc[nb][i];
     }
   }
 
