@@ -1469,8 +1469,8 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
     const uint32_t m = 1u << (col & 31);
     if (atomicOr(&bits32[tok * 2 * W + (col >> 5)], m) & m) return;
     ++my_ones;
-    // both counts of a column (at most kSmallN each) in one word until the
-    // paths are complete
+    // both counts of a column (at most kSmallN each) in one word: all tokens in
+    // the lower half, those of batch 1 as it came in the upper
     atomicAdd(&cnt_all[col], tok < n1 ? 0x10001 : 1);
   };
   // 16-byte pieces when rows allow it: the node's rows back to back (ids_in
@@ -1524,27 +1524,23 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
   }
   int tot_all = 0;
   (void)small_block_scan(my_ones, &tot_all, s_redi);  // its barriers publish bits and counts
-  for (int c = tid; c < LE; c += kSel) {
-    const int both = cnt_all[c];
-    cnt_orig[c] = both >> 16;
-    cnt_all[c] = both & 0xffff;
-  }
+  for (int c = tid; c < LE; c += kSel) cnt_orig[c] = cnt_all[c] >> 16;
+  auto count_of = [&](int col) { return cnt_all[col] & 0xffff; };
+
+  // per token: sum over its columns of cnt(column); accumulated into out[] (zeroed)
+  auto col_sums = [&](auto&& cnt, int* out) {
+    for (int q = tid; q < NW; q += kSel) {
+      const int lo = (q % W) * 64;
+      int sum = 0;
+      for (uint64_t x = bits[q]; x; x &= x - 1) sum += cnt(lo + __builtin_ctzll(x));
+      if (sum) atomicAdd(&out[q / W], sum);
+    }
+  };
   for (int q = tid; q < NW; q += kSel) {         // |r_i|
     const int c = __popcll(bits[q]);
     if (c) atomicAdd(&ones[q / W], c);
   }
-  __syncthreads();
-
-  // per token: sum over its columns of cnt[]; accumulated into out[] (zeroed)
-  auto col_sums = [&](const int* cnt, int* out) {
-    for (int q = tid; q < NW; q += kSel) {
-      const int lo = (q % W) * 64;
-      int sum = 0;
-      for (uint64_t x = bits[q]; x; x &= x - 1) sum += cnt[lo + __builtin_ctzll(x)];
-      if (sum) atomicAdd(&out[q / W], sum);
-    }
-  };
-  col_sums(cnt_all, sall);
+  col_sums(count_of, sall);
 
   int iters = 0, converged = 1, med0 = -1, med1 = -1;
   if (trivial) {                                 // one batch empty: the input split stands
@@ -1680,7 +1676,7 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
         }
       int tot1 = 0;
       (void)small_block_scan(my1, &tot1, s_redi);   // its barriers publish cnt1
-      col_sums(cnt1, s1);
+      col_sums([&](int col) { return cnt1[col]; }, s1);
       __syncthreads();
       med0 = m1;
       med1 = m2;
@@ -1707,8 +1703,8 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
   // Eq. 2 before and after, the guard
   int ob = 0, oa = 0;
   for (int col = tid; col < LE; col += kSel) {
-    ob += (cnt_orig[col] > 0) + (cnt_all[col] - cnt_orig[col] > 0);
-    oa += (cnt1[col] > 0) + (cnt_all[col] - cnt1[col] > 0);
+    ob += (cnt_orig[col] > 0) + (count_of(col) - cnt_orig[col] > 0);
+    oa += (cnt1[col] > 0) + (count_of(col) - cnt1[col] > 0);
   }
   int obj_before = 0, obj_after = 0;
   (void)small_block_scan(ob, &obj_before, s_redi);
@@ -1725,7 +1721,7 @@ sch_small(const uint8_t* __restrict__ routes, const SmallNodes nodes, int ids_in
     for (int col = tid; col < LE; col += kSel) {
       const int c = use_orig ? cnt_orig[col] : cnt1[col];
       demand[col] = c;
-      demand[LE + col] = cnt_all[col] - c;
+      demand[LE + col] = count_of(col) - c;
     }
   if (info && tid == 0) {
     info[0] = iters;
